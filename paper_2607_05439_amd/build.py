@@ -12,7 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["dcp_api.hip", "fast.hip", "proj.hip", "generic.hip", "merge.hip", "sparse.hip", "knn.hip", "transition.hip", "scatter.hip"]
+SOURCES = ["dcp_api.hip", "fast.hip", "proj.hip", "generic.hip", "merge.hip", "sparse.hip", "knn.hip", "transition.hip", "transition_f32.hip", "scatter.hip"]
 ARCH = ["--offload-arch=gfx950"]
 FLAGS = ["-O3", *ARCH, "-fPIC", "-std=c++17",
          # hipcc's host pass warns that it does not know this feature; harmless

@@ -318,46 +318,6 @@ __global__ void __launch_bounds__(64 * kWaves) trans_kernel(TransArgs a) {
   wait_vm<0>();
 }
 
-// ----------------------------------------------------------------------------- fp32 path
-// One wave per pair: LayerNorm, then 8+ hidden units per lane, h in LDS, then
-// the output channels per lane; fp32 throughout.
-__global__ void __launch_bounds__(256) trans_gen_kernel(TransGenArgs a) {
-  __shared__ float s_n[4][kGenMaxCz];
-  __shared__ float s_h[4][kTransGenMaxHidden];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t p = (int64_t)blockIdx.x * 4 + wave;
-  if (p >= a.n_pairs) return;
-  const float* z = a.z_in + p * a.c_z;
-  float s = 0.0f;
-  for (int c = lane; c < a.c_z; c += 64) s += z[c];
-  for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
-  const float mu = s / (float)a.c_z;
-  float v = 0.0f;
-  for (int c = lane; c < a.c_z; c += 64) v = fmaf(z[c] - mu, z[c] - mu, v);
-  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
-  const float rstd = 1.0f / sqrtf(v / (float)a.c_z + a.eps);
-  float* nn = s_n[wave];
-  for (int c = lane; c < a.c_z; c += 64)
-    nn[c] = (a.gamma ? a.gamma[c] : 1.0f) * ((z[c] - mu) * rstd) + (a.beta ? a.beta[c] : 0.0f);
-  __builtin_amdgcn_wave_barrier();
-  float* hh = s_h[wave];
-  for (int u = lane; u < a.hidden; u += 64) {
-    float x = 0.0f, y = 0.0f;
-    for (int c = 0; c < a.c_z; ++c) {
-      x = fmaf(a.w1[(int64_t)u * a.c_z + c], nn[c], x);
-      y = fmaf(a.w2[(int64_t)u * a.c_z + c], nn[c], y);
-    }
-    hh[u] = x / (1.0f + expf(-x)) * y;
-  }
-  __builtin_amdgcn_wave_barrier();
-  for (int c = lane; c < a.c_z; c += 64) {
-    float t = 0.0f;
-    for (int u = 0; u < a.hidden; ++u) t = fmaf(a.w3[(int64_t)c * a.hidden + u], hh[u], t);
-    a.z_out[p * a.c_z + c] = z[c] + t;
-  }
-}
-
 }  // namespace
 
 size_t trans_prep_bytes() { return (size_t)kHt * kTileBytes + 2 * kCz * sizeof(float); }
@@ -370,11 +330,6 @@ hipError_t launch_transition(const TransArgs& a, hipStream_t st) {
   const int64_t n_groups = (a.n_pairs + kGroupPairs - 1) / kGroupPairs;
   const int64_t grid = n_groups < 256 ? n_groups : 256;  // one persistent workgroup per CU
   hipLaunchKernelGGL(trans_kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_transition_gen(const TransGenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(trans_gen_kernel, dim3((unsigned)((a.n_pairs + 3) / 4)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

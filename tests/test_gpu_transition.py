@@ -113,3 +113,34 @@ def test_bf16_full_size_in_place_sampled():
     assert err <= 1e-2
     del z
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("c_z,hidden", [(4, 16), (20, 48), (32, 128), (64, 80), (100, 400), (128, 512), (132, 16),
+                                        (256, 1024), (30, 64), (32, 72)])
+def test_f32_widths_and_tile_edges(c_z, hidden):
+    """fp32 widths on both kernels (c_z a multiple of 4 and hidden of 16, or
+    not) and every template width, pair counts around the 16- and 32-pair tiles
+    and the rule between them; a weight off 16-byte alignment gives the vector
+    kernel's result. Tolerance: the fp32 acceptance bound (1e-5 of the largest
+    value), far above sqrt(hidden) * 2^-24."""
+    import torch
+    rng = np.random.default_rng(c_z * 1000 + hidden)
+    w = {"w1": rng.standard_normal((hidden, c_z)) / np.sqrt(c_z), "w2": rng.standard_normal((hidden, c_z)) / np.sqrt(c_z),
+         "w3": rng.standard_normal((c_z, hidden)) / np.sqrt(hidden), "gamma": 1 + 0.25 * rng.standard_normal(c_z),
+         "beta": 0.25 * rng.standard_normal(c_z)}
+    w = {k: v.astype(np.float32) for k, v in w.items()}
+    for n in (1, 15, 17, 33) + ((12288, 12289) if c_z == 32 else ()):
+        z = rng.standard_normal((n, c_z)).astype(np.float32)
+        ref = oracle.transition(z, w["w1"], w["w2"], w["w3"], w["gamma"], w["beta"])
+        zt = dev(z)
+        got = run(zt, w, DCP_F32)
+        assert rel_err(host_f64(got), ref) <= 1e-5
+        assert torch.equal(run(zt.clone(), w, DCP_F32, in_place=True), got)
+    import paper_2607_05439_amd as dcp
+    off = torch.empty(hidden * c_z + 1, device="cuda:0")
+    off[1:] = dev(w["w1"]).reshape(-1)
+    out = torch.empty_like(zt)
+    W = {k: dev(v) for k, v in w.items()}
+    dcp.dcp_pair_transition(n, c_z, hidden, DCP_F32, 1e-5, off[1:], W["w2"], W["w3"], W["gamma"], W["beta"], zt, out,
+                            None, 0)
+    assert rel_err(host_f64(out), ref) <= 1e-5
