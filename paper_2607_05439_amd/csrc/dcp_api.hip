@@ -215,6 +215,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
   const bool act_bf16 = shape->act_dtype == DCP_BF16;
   hipError_t e;
   const int32_t log2_units = path == kPathFast ? 1 : 0;
+  bool merged = false;  // the attention kernel already wrote the result
   if (path == kPathFast) {
     dcp::FastProjArgs pa{};
     pa.s = static_cast<const uint16_t*>(s);
@@ -276,6 +277,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.q_row0 = q_row0;
     pa.n_q = n_q;
     pa.c_s = shape->c_s;
+    pa.mask = key_mask;
     pa.hd = hd;
     pa.q = reinterpret_cast<float*>(ws + L.off_q);
     pa.k = reinterpret_cast<float*>(ws + L.off_k);
@@ -299,11 +301,30 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     aa.head_dim = shape->head_dim;
     aa.k_lo = k_lo;
     aa.k_len = k_len;
-    aa.n_kb = n_key_blocks;
+    // A workgroup of the tiled kernel holds one query row: with a row for every CU the key blocks
+    // are folded in one pass over the row's keys (any partition gives the same
+    // result up to rounding); with fewer, each block is a workgroup of its own.
+    // A single part is normalised, or written as the caller's partial state, by
+    // the attention itself.
+    const bool tiled = dcp::gen_attn_tiled(shape->c_z, shape->n_heads, shape->head_dim);
+    if (tiled && n_q >= kSchedCUs) L.n_parts = 1;
+    aa.n_parts = L.n_parts;
     aa.eps = shape->ln_eps;
     aa.m_parts = reinterpret_cast<float*>(ws + L.off_m);
     aa.l_parts = reinterpret_cast<float*>(ws + L.off_l);
     aa.acc_parts = reinterpret_cast<float*>(ws + L.off_acc);
+    if (tiled && L.n_parts == 1 && k_len > 0) {
+      merged = true;
+      if (part) {
+        aa.m_parts = part->m;
+        aa.l_parts = part->l;
+        aa.acc_parts = part->acc;
+      } else {
+        aa.g = pa.g;
+        aa.out = out;
+        aa.out_bf16 = shape->out_dtype == DCP_BF16;
+      }
+    }
     if (g_ev_start && (e = hipEventRecord(static_cast<hipEvent_t>(g_ev_start), st)) != hipSuccess)
       return fail(DCP_ERR_HIP, "hipEventRecord failed: %s", hipGetErrorString(e));
     if (k_len > 0 && (e = dcp::launch_gen_attn(aa, st)) != hipSuccess)
@@ -333,7 +354,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     ma.out = out;
     ma.out_bf16 = shape->out_dtype == DCP_BF16;
   }
-  if ((e = dcp::launch_merge(ma, st)) != hipSuccess)
+  if (!merged && (e = dcp::launch_merge(ma, st)) != hipSuccess)
     return fail(DCP_ERR_HIP, "merge launch failed: %s", hipGetErrorString(e));
   return ok();
 }

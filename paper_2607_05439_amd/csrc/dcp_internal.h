@@ -94,7 +94,9 @@ struct GenProjArgs {
   const float *w_q, *w_k, *w_v, *w_g;
   int64_t n_tok, q_row0, n_q;
   int32_t c_s, hd;
-  float *q, *k, *v, *g;  // q, g: [n_q][hd]; k, v: [N][hd]; g holds the sigmoid
+  float *q, *k, *v, *g;  // q, g: [n_q][hd]; k, v: [N][hd]; g holds the sigmoid (16-byte aligned)
+  const uint8_t* mask;   // [N] or null: v of masked keys is written as 0
+  int32_t s_vec;         // set by the launcher: rows of s take 4-element loads
 };
 
 struct GenAttnArgs {
@@ -104,10 +106,13 @@ struct GenAttnArgs {
   const float *w_b, *gamma;
   const float *q, *k, *v;
   int64_t n_tok, n_q;
-  int64_t k_lo, k_len;  // keys [k_lo, k_lo + k_len), split into n_kb blocks
-  int32_t c_z, n_heads, head_dim, n_kb;
+  int64_t k_lo, k_len;  // keys [k_lo, k_lo + k_len), split into n_parts parts
+  int32_t c_z, n_heads, head_dim, n_parts;
   float eps;
   float *m_parts, *l_parts, *acc_parts;
+  const float* g;       // with out: the gate [n_q][hd]
+  void* out;            // n_parts = 1: the gated, normalised output in place of the partial state; else null
+  int32_t out_bf16;
 };
 
 struct GenBiasArgs {
@@ -235,6 +240,7 @@ hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st);
 hipError_t launch_fast_attn(const FastAttnArgs& a, hipStream_t st);
 hipError_t launch_fast_bias(const FastBiasArgs& a, hipStream_t st);
 hipError_t launch_gen_proj(const GenProjArgs& a, hipStream_t st);
+bool gen_attn_tiled(int32_t c_z, int32_t n_heads, int32_t head_dim);
 hipError_t launch_gen_attn(const GenAttnArgs& a, hipStream_t st);
 hipError_t launch_gen_bias(const GenBiasArgs& a, hipStream_t st);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);

@@ -1,11 +1,12 @@
 // General fp32 path: any c_z <= 256, H <= 16, d <= 64, H*d <= 128, with s and
-// z in fp32 or bf16. Plain vector-ALU kernels with fp32 arithmetic throughout
-// (two-pass LayerNorm, expf), for the small and odd shapes the fused bf16
-// kernels do not cover. Partial states use natural-log units.
+// z in fp32 or bf16, for the shapes the fused bf16 kernels do not cover. fp32
+// arithmetic throughout (two-pass LayerNorm, expf); the projections and the pair
+// bias run on the fp32 matrix cores. Partial states use natural-log units.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include "cdna4.h"
 #include "dcp_internal.h"
 
 namespace dcp {
@@ -16,34 +17,142 @@ __device__ __forceinline__ float load_act(const void* p, int bf16, int64_t idx) 
   return static_cast<const float*>(p)[idx];
 }
 
-// One thread per (token, output) of the four projections; grid-stride.
-__global__ void __launch_bounds__(256) gen_proj_kernel(GenProjArgs a) {
-  const int64_t per_kv = a.n_tok * a.hd, per_q = a.n_q * a.hd;
-  const int64_t total = 2 * per_kv + 2 * per_q;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    int which;
-    int64_t r;
-    if (t < per_kv) {
-      which = 1;
-      r = t;
-    } else if (t < 2 * per_kv) {
-      which = 2;
-      r = t - per_kv;
-    } else if (t < 2 * per_kv + per_q) {
-      which = 0;
-      r = t - 2 * per_kv;
+// v_mfma_f32_16x16x4_f32: A holds row n, B column n (n = lane % 16), both at
+// k-slot g = lane / 16; the accumulator holds rows 4g..4g+3 of column n.
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Four consecutive elements at p + i0 as loaded (fp32: 16 bytes, bf16: 8), or
+// one by one, indices past the last repeating it, where the row length is not a
+// multiple of four. Kept apart from the conversion so that loads can be
+// issued ahead of their use.
+__device__ __forceinline__ u32x4 load_raw4(const void* p, int bf16, int vec, int64_t base, int i0, int len) {
+  u32x4 r;
+  if (vec) {
+    if (bf16) {
+      const u32x2 t = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p) + base + i0);
+      r[0] = t[0], r[1] = t[1], r[2] = 0u, r[3] = 0u;
     } else {
-      which = 3;
-      r = t - 2 * per_kv - per_q;
+      r = *reinterpret_cast<const u32x4*>(static_cast<const float*>(p) + base + i0);
     }
-    const int64_t row = r / a.hd;
-    const int o = (int)(r - row * a.hd);
-    const int64_t tok = (which == 0 || which == 3) ? a.q_row0 + row : row;
-    const float* w = which == 0 ? a.w_q : which == 1 ? a.w_k : which == 2 ? a.w_v : a.w_g;
-    float acc = 0.0f;
-    for (int c = 0; c < a.c_s; ++c) acc = fmaf(w[(int64_t)o * a.c_s + c], load_act(a.s, a.s_bf16, tok * a.c_s + c), acc);
-    float* dst = which == 0 ? a.q : which == 1 ? a.k : which == 2 ? a.v : a.g;
-    dst[r] = which == 3 ? 1.0f / (1.0f + expf(-acc)) : acc;
+  } else {
+    uint32_t e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t x = base + min(i0 + i, len - 1);
+      e[i] = bf16 ? (uint32_t)static_cast<const uint16_t*>(p)[x] : static_cast<const uint32_t*>(p)[x];
+    }
+    if (bf16)
+      r[0] = e[0] | (e[1] << 16), r[1] = e[2] | (e[3] << 16), r[2] = 0u, r[3] = 0u;
+    else
+      r[0] = e[0], r[1] = e[1], r[2] = e[2], r[3] = e[3];
+  }
+  return r;
+}
+__device__ __forceinline__ f32x4 raw4_to_f32(const u32x4& r, int bf16) {
+  f32x4 v;
+  if (bf16) {
+    v[0] = __uint_as_float(r[0] << 16), v[1] = __uint_as_float(r[0] & 0xFFFF0000u);
+    v[2] = __uint_as_float(r[1] << 16), v[3] = __uint_as_float(r[1] & 0xFFFF0000u);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(r[i]);
+  }
+  return v;
+}
+
+// The four projections on the fp32 matrix cores: each wave forms T x T tiles of
+// 16 outputs (rows of W, the A operand) by 16 tokens (the B operand); channel
+// 16j + 4g + i is k-slot g of step (j, i), so both operands are plain 16-byte
+// loads of a row, eight of each in flight. Blocks: 4 waves of consecutive output
+// tiles over the same tokens; the side (k and v over all tokens, q and g over
+// the query rows) comes from the block index. With one thread per output,
+// reading its row of W alone, 128 tokens took 20 us.
+template <int T>
+__global__ void __launch_bounds__(256) gen_proj_kernel(GenProjArgs a) {
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_ot = (a.hd + 16 * T - 1) / (16 * T);  // output tiles of one projection
+  const int ot = (int)(blockIdx.y * 4 + wave);       // tiles of the side's two projections
+  if (ot >= 2 * n_ot) return;
+  const int64_t kv_tiles = (a.n_tok + 16 * T - 1) / (16 * T);
+  const bool q_side = blockIdx.x >= kv_tiles;
+  const int64_t row0 = ((int64_t)blockIdx.x - (q_side ? kv_tiles : 0)) * (16 * T);
+  const int64_t rows = q_side ? a.n_q : a.n_tok;
+  const bool second = ot >= n_ot;
+  const int o0 = (second ? ot - n_ot : ot) * (16 * T);
+  const float* w = q_side ? (second ? a.w_g : a.w_q) : (second ? a.w_v : a.w_k);
+  float* dst = q_side ? (second ? a.g : a.q) : (second ? a.v : a.k);
+  const bool w_vec = a.s_vec && (reinterpret_cast<uintptr_t>(w) & 15) == 0;
+  int64_t s_base[T], w_base[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    s_base[t] = ((q_side ? a.q_row0 : 0) + min(row0 + 16 * t + n, rows - 1)) * a.c_s;
+    w_base[t] = (int64_t)min(o0 + 16 * t + n, a.hd - 1) * a.c_s;
+  }
+  f32x4 acc[T][T];
+#pragma unroll
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int kC = 8 / T;  // chunks of 16 channels per step
+  for (int c0 = 0; c0 < a.c_s; c0 += 16 * kC) {
+    u32x4 sr[T][kC], wr[T][kC];
+#pragma unroll
+    for (int j = 0; j < kC; ++j) {
+      const int ch = c0 + 16 * j + 4 * g;
+      const int at = a.s_vec ? min(ch, a.c_s - 4) : ch;  // past the row: any element of it, times 0
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        sr[t][j] = load_raw4(a.s, a.s_bf16, a.s_vec, s_base[t], at, a.c_s);
+        wr[t][j] = load_raw4(w, 0, w_vec, w_base[t], at, a.c_s);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kC; ++j) {
+      f32x4 sv[T], wv[T];
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        sv[t] = raw4_to_f32(sr[t][j], a.s_bf16);
+        wv[t] = raw4_to_f32(wr[t][j], 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool in = c0 + 16 * j + 4 * g + i < a.c_s;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          sv[t][i] = in ? sv[t][i] : 0.0f;
+          wv[t][i] = in ? wv[t][i] : 0.0f;
+        }
+#pragma unroll
+        for (int x = 0; x < T; ++x)
+#pragma unroll
+          for (int y = 0; y < T; ++y) acc[x][y] = mfma4(wv[x][i], sv[y][i], acc[x][y]);
+      }
+    }
+  }
+#pragma unroll
+  for (int y = 0; y < T; ++y) {
+    const int64_t row = row0 + 16 * y + n;
+    if (row >= rows) continue;
+#pragma unroll
+    for (int x = 0; x < T; ++x) {
+      const int o = o0 + 16 * x + 4 * g;
+      f32x4 v = acc[x][y];
+      if (q_side && second)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = 1.0f / (1.0f + expf(-v[i]));
+      // a masked key's v: 0, as its weight is (0 times a NaN would be one)
+      if (!q_side && second && a.mask && a.mask[row] == 0) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (a.hd % 4 == 0) {
+        if (o < a.hd) *reinterpret_cast<f32x4*>(dst + row * a.hd + o) = v;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (o + i < a.hd) dst[row * a.hd + o + i] = v[i];
+      }
+    }
   }
 }
 
@@ -61,10 +170,11 @@ __device__ __forceinline__ void ln_stats(const void* z, int bf16, int64_t off, i
   rstd = 1.0f / sqrtf(v / (float)c_z + eps);
 }
 
-// grid (n_q rows, n_kb parts), one wave. Each lane owns keys start+lane,
+// The shapes the tiled kernel below does not take: grid (n_q rows, n_parts
+// parts), one wave. Each lane owns keys start+lane,
 // start+lane+64, ... with its own online-softmax state in LDS; the 64 states
 // are then merged in lane order.
-__global__ void __launch_bounds__(64) gen_attn_kernel(GenAttnArgs a) {
+__global__ void __launch_bounds__(64) gen_attn_any_kernel(GenAttnArgs a) {
   __shared__ float wg[kGenMaxH * kGenMaxCz];  // W_b * gamma
   __shared__ float st_m[64][kGenMaxH];
   __shared__ float st_l[64][kGenMaxH];
@@ -82,7 +192,7 @@ __global__ void __launch_bounds__(64) gen_attn_kernel(GenAttnArgs a) {
   __syncthreads();
 
   int64_t size, start;
-  chunk_of(a.k_len, a.n_kb, part, &size, &start);
+  chunk_of(a.k_len, a.n_parts, part, &size, &start);
   start += a.k_lo;
   const float scale = 1.0f / sqrtf((float)d);
   const float* qr = a.q + row * hd;
@@ -128,6 +238,234 @@ __global__ void __launch_bounds__(64) gen_attn_kernel(GenAttnArgs a) {
   }
 }
 
+// Four consecutive elements of z as loaded, and as fp32.
+template <bool BF16>
+struct RawZ;
+template <>
+struct RawZ<false> {
+  typedef f32x4 type;
+  static __device__ __forceinline__ type load(const void* p, int64_t i) {
+    return *reinterpret_cast<const f32x4*>(static_cast<const float*>(p) + i);
+  }
+  static __device__ __forceinline__ f32x4 to_f32(const type& r) { return r; }
+};
+template <>
+struct RawZ<true> {
+  typedef u32x2 type;
+  static __device__ __forceinline__ type load(const void* p, int64_t i) {
+    return *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p) + i);
+  }
+  static __device__ __forceinline__ f32x4 to_f32(const type& r) {
+    return f32x4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xFFFF0000u), __uint_as_float(r[1] << 16),
+                 __uint_as_float(r[1] & 0xFFFF0000u)};
+  }
+};
+
+// grid (n_q rows, parts), 4 waves that share one query row and take every
+// fourth tile of 16 keys of the part. Lane (n, g) holds key n of the tile.
+//  - z: the tile's 16 pair vectors are consecutive in memory; the lane loads
+//    channels 16j + 4g .. +3 of its key (one tile ahead) and the four lanes of a
+//    key form its two-pass LayerNorm statistics.
+//  - bias on the fp32 matrix cores: A = W_b gamma with head 4 (n % 4) + n / 4 in
+//    row n, B = z - mean as loaded; accumulator register i of lane (n, g) is then
+//    head 4i + g of key n, so each lane owns NH = ceil(H / 4) heads of one key,
+//  - and the logits, an online softmax of the lane's own keys and the weighted
+//    sum of v run in the lane, with k and v read straight from L2 in 16-byte
+//    loads and no exchange between lanes until the row's end.
+// The 16 lanes' and 4 waves' states meet in LDS, in a fixed order.
+// DP: the head size padded to a multiple of 4; c_z <= 16 CT.
+// What bounds it: one row per workgroup reads k and v (1 KB a key at 4 x 32) from
+// L2 beside each key's z; a lane per key and its state in LDS, with z read three
+// times in 4-byte pieces, took 1810 us on 601 tokens of 128 channels.
+template <int NH, int DP, int CT, bool BF16>
+__global__ void __launch_bounds__(256, 2) gen_attn_kernel(GenAttnArgs a) {
+  constexpr int kHd = 4 * NH * DP;  // padded channels of all lanes' heads
+  constexpr int kQs = DP + 4;       // q row stride: the four heads read at once fall in different banks
+  __shared__ __align__(16) float s_q[4 * NH * kQs];
+  __shared__ __align__(16) float s_w[16 * 16 * CT];  // [j][lane][4]: A operands
+  __shared__ __align__(16) float s_o[4][16][kHd];
+  __shared__ float s_l[4][16][4 * NH];
+  __shared__ float s_m[4][4 * NH];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row = blockIdx.x;
+  const int part = blockIdx.y;
+  const int H = a.n_heads, d = a.head_dim, hd = H * d, c_z = a.c_z;
+  int64_t size, start;
+  chunk_of(a.k_len, a.n_parts, part, &size, &start);
+  start += a.k_lo;
+  const int64_t end = start + size;
+  const int64_t n_tiles = (size + 15) / 16;
+
+  // Chunks past c_z or d repeat the last one: no load is conditional. fm is 0
+  // there (and so are the weights and q), else 1.
+  typedef typename RawZ<BF16>::type raw_t;
+  raw_t zr[CT];
+  float fm[CT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j) fm[j] = 16 * j < c_z ? 1.0f : 0.0f;
+  auto load_z = [&](int64_t t) {
+    const int64_t key = min(start + 16 * t + n, end - 1);
+    const int64_t base = (row * a.n_tok + key) * c_z + 4 * g;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) zr[j] = RawZ<BF16>::load(a.z, base + min(16 * j, c_z - 16));
+  };
+  if (wave < n_tiles) load_z(wave);
+
+  for (int x = tid; x < 4 * NH * kQs; x += 256) {
+    const int h = x / kQs, e = x % kQs;
+    s_q[x] = h < H && e < d ? a.q[row * hd + h * d + e] : 0.0f;
+  }
+  for (int x = tid; x < 16 * 16 * CT; x += 256) {
+    const int l = (x >> 2) & 63, c = 16 * (x >> 8) + 4 * (l >> 4) + (x & 3), r = l & 15;
+    const int h = 4 * (r & 3) + (r >> 2);
+    s_w[x] = h < H && c < c_z ? a.w_b[h * c_z + c] * (a.gamma ? a.gamma[c] : 1.0f) : 0.0f;
+  }
+  __syncthreads();
+
+  const float scale = 1.0f / sqrtf((float)d), inv_cz = 1.0f / (float)c_z;
+  float m[NH], l[NH];
+  f32x4 o[NH][DP / 4];
+  int head[NH];  // offset of the lane's heads (past the last: the last)
+#pragma unroll
+  for (int i = 0; i < NH; ++i) {
+    m[i] = -INFINITY;
+    l[i] = 0.0f;
+    head[i] = min(4 * i + g, H - 1) * d;
+#pragma unroll
+    for (int c = 0; c < DP / 4; ++c) o[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  for (int64_t t = wave; t < n_tiles; t += 4) {
+    const int64_t key = start + 16 * t + n;
+    const int64_t kk = min(key, end - 1);
+    const bool valid = key < end && (!a.mask || a.mask[kk] != 0);
+    const float *kp = a.k + kk * hd, *vp = a.v + kk * hd;
+    // k of this tile, requested before the work on z
+    f32x4 kr[NH][DP / 4], vr[NH][DP / 4];
+#pragma unroll
+    for (int i = 0; i < NH; ++i)
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c) kr[i][c] = *reinterpret_cast<const f32x4*>(kp + head[i] + min(4 * c, d - 4));
+    f32x4 z[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) z[j] = RawZ<BF16>::to_f32(zr[j]);
+    load_z(min(t + 4, n_tiles - 1));
+    float s = 0.0f, v = 0.0f;
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s = fmaf(z[j][i], fm[j], s);
+    const float mu = sum4(s) * inv_cz;
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        z[j][i] = fmaf(z[j][i], fm[j], -mu * fm[j]);
+        v = fmaf(z[j][i], z[j][i], v);
+      }
+    const float rstd = 1.0f / sqrtf(fmaf(sum4(v), inv_cz, a.eps));
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(&s_w[(j * 64 + lane) * 4]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b = mfma4(w[i], z[j][i], b);
+    }
+#pragma unroll
+    for (int i = 0; i < NH; ++i)
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c) vr[i][c] = *reinterpret_cast<const f32x4*>(vp + head[i] + min(4 * c, d - 4));
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      float dot = 0.0f;
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c) {
+        const f32x4 q = *reinterpret_cast<const f32x4*>(&s_q[(4 * i + g) * kQs + 4 * c]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot = fmaf(q[e], kr[i][c][e], dot);
+      }
+      const float lg = valid ? fmaf(b[i], rstd, dot * scale) : -INFINITY;
+      const float mn = fmaxf(m[i], lg);
+      const float base = mn == -INFINITY ? 0.0f : mn;
+      const float al = expf(m[i] - base);  // 0 when m = -inf
+      const float p = expf(lg - base);     // 0 for a masked key, whose v the projection zeroed
+      l[i] = fmaf(l[i], al, p);
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[i][c][e] = fmaf(p, vr[i][c][e], o[i][c][e] * al);
+      m[i] = mn;
+    }
+  }
+
+  // the lane's state relative to the wave's maximum, then all of them by channel
+#pragma unroll
+  for (int i = 0; i < NH; ++i) {
+    float mx = m[i];
+#pragma unroll
+    for (int x = 8; x >= 1; x >>= 1) mx = fmaxf(mx, __shfl_xor(mx, x, 16));
+    const float f = expf(m[i] - (mx == -INFINITY ? 0.0f : mx));
+    s_l[wave][n][4 * i + g] = l[i] * f;
+    if (n == 0) s_m[wave][4 * i + g] = mx;
+#pragma unroll
+    for (int c = 0; c < DP / 4; ++c)
+      *reinterpret_cast<f32x4*>(&s_o[wave][n][(4 * i + g) * DP + 4 * c]) = o[i][c] * f;
+  }
+  __syncthreads();
+  for (int x = tid; x < hd; x += 256) {
+    const int h = x / d, e = x - h * d;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, s_m[w][h]);
+    float ls = 0.0f, acc = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = expf(s_m[w][h] - (mx == -INFINITY ? 0.0f : mx));
+      float lw = 0.0f, ow = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        lw += s_l[w][i][h];
+        ow += s_o[w][i][h * DP + e];
+      }
+      ls = fmaf(f, lw, ls);
+      acc = fmaf(f, ow, acc);
+    }
+    const int64_t at = row * hd + x;
+    if (a.out) {  // one part: gate and normalise here
+      const float r = ls == 0.0f ? 0.0f : a.g[at] * (acc / ls);
+      if (a.out_bf16)
+        static_cast<__bf16*>(a.out)[at] = (__bf16)r;
+      else
+        static_cast<float*>(a.out)[at] = r;
+    } else {
+      a.acc_parts[(int64_t)part * a.n_q * hd + at] = acc;
+      if (e == 0) {
+        a.m_parts[((int64_t)part * H + h) * a.n_q + row] = mx;
+        a.l_parts[((int64_t)part * H + h) * a.n_q + row] = ls;
+      }
+    }
+  }
+}
+
+template <int NH, int DP, bool BF16>
+void gen_attn_launch(const GenAttnArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)a.n_q, (unsigned)a.n_parts);
+  if (a.c_z <= 32)
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 2, BF16>), grid, dim3(256), 0, st, a);
+  else if (a.c_z <= 64)
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 4, BF16>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 8, BF16>), grid, dim3(256), 0, st, a);
+}
+template <int NH, int DP>
+void gen_attn_launch(const GenAttnArgs& a, hipStream_t st) {
+  if (a.z_bf16)
+    gen_attn_launch<NH, DP, true>(a, st);
+  else
+    gen_attn_launch<NH, DP, false>(a, st);
+}
+
 // One thread per pair: the full bias with the LayerNorm affine and b_b.
 __global__ void __launch_bounds__(256) gen_bias_kernel(GenBiasArgs a) {
   const int64_t total = a.n_rows * a.n_cols;
@@ -157,13 +495,42 @@ int grid_for(int64_t items) {
 }  // namespace
 
 hipError_t launch_gen_proj(const GenProjArgs& a, hipStream_t st) {
-  const int64_t total = 2 * a.n_tok * a.hd + 2 * a.n_q * a.hd;
-  hipLaunchKernelGGL(gen_proj_kernel, dim3(grid_for(total)), dim3(256), 0, st, a);
+  GenProjArgs b = a;
+  b.s_vec = a.c_s % 4 == 0;  // s itself is 16-byte aligned
+  // One 16 x 16 tile per wave while that leaves the chip short of waves (2048 =
+  // two per SIMD), 2 x 2 beyond: each loaded operand then serves two products.
+  const int64_t tiles = ((a.n_tok + 15) / 16 + (a.n_q + 15) / 16) * 2 * ((a.hd + 15) / 16);
+  const int t = tiles <= 2048 ? 1 : 2;
+  const int n_ot = (a.hd + 16 * t - 1) / (16 * t);
+  const int64_t blocks = (a.n_tok + 16 * t - 1) / (16 * t) + (a.n_q + 16 * t - 1) / (16 * t);
+  const dim3 grid((unsigned)blocks, (unsigned)((2 * n_ot + 3) / 4));
+  if (t == 1)
+    hipLaunchKernelGGL(gen_proj_kernel<1>, grid, dim3(256), 0, st, b);
+  else
+    hipLaunchKernelGGL(gen_proj_kernel<2>, grid, dim3(256), 0, st, b);
   return hipGetLastError();
 }
 
+// The tiled kernel takes pair widths of whole 16-channel chunks up to 128 and
+// the head shapes whose k, v and accumulators (heads per lane times head size)
+// fit its registers: up to 4 heads of 32, 8 of 16 or 16 of 8.
+bool gen_attn_tiled(int32_t c_z, int32_t n_heads, int32_t head_dim) {
+  const int per_lane = (n_heads + 3) / 4;
+  return c_z % 16 == 0 && c_z <= 128 && head_dim % 4 == 0 &&
+         head_dim <= (per_lane == 1 ? 32 : per_lane == 2 ? 16 : 8);
+}
+
 hipError_t launch_gen_attn(const GenAttnArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(gen_attn_kernel, dim3((unsigned)a.n_q, (unsigned)a.n_kb), dim3(64), 0, st, a);
+  if (!gen_attn_tiled(a.c_z, a.n_heads, a.head_dim))
+    hipLaunchKernelGGL(gen_attn_any_kernel, dim3((unsigned)a.n_q, (unsigned)a.n_parts), dim3(64), 0, st, a);
+  else if (a.n_heads > 8)
+    gen_attn_launch<4, 8>(a, st);
+  else if (a.n_heads > 4)
+    gen_attn_launch<2, 16>(a, st);
+  else if (a.head_dim > 16)
+    gen_attn_launch<1, 32>(a, st);
+  else
+    gen_attn_launch<1, 16>(a, st);
   return hipGetLastError();
 }
 

@@ -54,6 +54,38 @@ def test_general_path_bf16_inputs(torch_cuda):
     assert rel_err(got, ref) <= TOL_F32
 
 
+@pytest.mark.parametrize("n_tok,c_s,c_z,h,d,dtype,n_kb", [
+    # the tiled kernel: every head layout, pair widths at and between its templates, key tiles
+    # of 16 over 4 waves (1, 15, 17, 64, 65 keys), rows on both sides of the one-pass rule (256)
+    (1, 16, 16, 1, 4, "f32", 1), (15, 33, 32, 3, 12, "f32", 2), (17, 128, 48, 4, 32, "f32", 3),
+    (64, 64, 64, 5, 16, "f32", 1), (65, 70, 96, 8, 16, "bf16", 5), (100, 128, 112, 16, 8, "f32", 4),
+    (90, 36, 128, 9, 8, "bf16", 1), (255, 128, 128, 4, 32, "f32", 3), (257, 96, 32, 4, 16, "f32", 3),
+    # shapes it does not take: the general kernel
+    (40, 20, 24, 2, 6, "f32", 3), (33, 128, 144, 2, 64, "f32", 2), (260, 48, 40, 10, 12, "bf16", 2)])
+def test_general_path_shapes(torch_cuda, n_tok, c_s, c_z, h, d, dtype, n_kb):
+    """Whole layers of the general path with an affine LayerNorm, masked keys whose s and z hold
+    NaN, and the ranges of a ring; the fp32 acceptance bound."""
+    log(f"case general path N={n_tok} c_s={c_s} c_z={c_z} H={h} d={d} {dtype} n_kb={n_kb}")
+    n_mask = n_tok // 7
+    wl = workload(n_tok=n_tok, c_s=c_s, c_z=c_z, n_heads=h, head_dim=d, dtype=dtype,
+                  mask=f"random:{n_mask}" if n_mask else "none")
+    dv = Device(wl, affine=True)
+    rows = np.arange(n_tok) if dv.mask_host is None else np.flatnonzero(dv.mask_host)
+    ref = dv.oracle_rows(rows)
+    if n_mask:
+        masked = torch_cuda.from_numpy(dv.mask_host == 0).cuda()
+        dv.z[:, masked] = float("nan")
+        dv.s[masked] = float("nan")
+    got = _np(dv.attention(0, n_tok, n_kb))[rows]
+    assert rel_err(got, ref) <= TOL_F32
+    assert rel_err(_np(dv.attention(0, n_tok, 1))[rows], got) <= TOL_BLOCKED
+    assert np.array_equal(_np(dv.attention(0, n_tok, n_kb))[rows], got)
+    if n_tok > 20:  # a stripe, bf16 output
+        sub = rows[(rows >= 3) & (rows < n_tok - 2)]
+        out = _np(dv.attention(3, n_tok - 5, n_kb, out_dtype=DCP_BF16))[sub - 3]
+        assert rel_err(out, ref[np.isin(rows, sub)]) <= TOL_BF16
+
+
 # ----------------------------------------------------------------------------- fused bf16 path
 def test_pad1024_parity(torch_cuda):
     log("case pad1024_bf16 n_kb=4 f32 out")
