@@ -277,7 +277,9 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.q_row0 = q_row0;
     pa.n_q = n_q;
     pa.c_s = shape->c_s;
+    const bool tiled = dcp::gen_attn_tiled(shape->c_z, shape->n_heads, shape->head_dim);
     pa.mask = key_mask;
+    pa.kv_head_dim = tiled ? shape->head_dim : 0;
     pa.hd = hd;
     pa.q = reinterpret_cast<float*>(ws + L.off_q);
     pa.k = reinterpret_cast<float*>(ws + L.off_k);
@@ -306,7 +308,6 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     // result up to rounding); with fewer, each block is a workgroup of its own.
     // A single part is normalised, or written as the caller's partial state, by
     // the attention itself.
-    const bool tiled = dcp::gen_attn_tiled(shape->c_z, shape->n_heads, shape->head_dim);
     if (tiled && n_q >= kSchedCUs) L.n_parts = 1;
     aa.n_parts = L.n_parts;
     aa.eps = shape->ln_eps;

@@ -96,6 +96,7 @@ struct GenProjArgs {
   int32_t c_s, hd;
   float *q, *k, *v, *g;  // q, g: [n_q][hd]; k, v: [N][hd]; g holds the sigmoid (16-byte aligned)
   const uint8_t* mask;   // [N] or null: v of masked keys is written as 0
+  int32_t kv_head_dim;   // k, v in the tiled attention's layout, with this head size; 0: row-major [N][hd]
   int32_t s_vec;         // set by the launcher: rows of s take 4-element loads
 };
 

@@ -62,6 +62,19 @@ __device__ __forceinline__ f32x4 raw4_to_f32(const u32x4& r, int bf16) {
   return v;
 }
 
+// k and v for the tiled attention: per 16 keys [heads by fours][4-channel
+// piece][key][head of the four][4], so that the piece c of four heads that the
+// 64 lanes load at once is 1 KB of consecutive memory (row-major, each lane's 16
+// bytes lay in a cache line of their own). The last keys and heads are packed
+// without padding: n_tok * H * d floats in all. Offset of piece 0 of head h of a
+// key, and the step from piece to piece.
+__device__ __forceinline__ int64_t kv_tile_offset(int64_t key, int64_t n_tok, int h, int H, int d, int* step) {
+  const int64_t t = key >> 4;
+  const int keys = (int)min((int64_t)16, n_tok - 16 * t), heads = min(4, H - (h & ~3));
+  *step = 4 * keys * heads;
+  return t * 16 * H * d + (int64_t)(h & ~3) * d * keys + ((int)(key & 15) * heads + (h & 3)) * 4;
+}
+
 // The four projections on the fp32 matrix cores: each wave forms T x T tiles of
 // 16 outputs (rows of W, the A operand) by 16 tokens (the B operand); channel
 // 16j + 4g + i is k-slot g of step (j, i), so both operands are plain 16-byte
@@ -145,7 +158,14 @@ __global__ void __launch_bounds__(256) gen_proj_kernel(GenProjArgs a) {
         for (int i = 0; i < 4; ++i) v[i] = 1.0f / (1.0f + expf(-v[i]));
       // a masked key's v: 0, as its weight is (0 times a NaN would be one)
       if (!q_side && second && a.mask && a.mask[row] == 0) v = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (a.hd % 4 == 0) {
+      if (a.kv_head_dim && !q_side) {
+        if (o < a.hd) {
+          const int h = o / a.kv_head_dim, c = (o - h * a.kv_head_dim) >> 2;
+          int step;
+          const int64_t at = kv_tile_offset(row, a.n_tok, h, a.hd / a.kv_head_dim, a.kv_head_dim, &step);
+          *reinterpret_cast<f32x4*>(dst + at + c * step) = v;
+        }
+      } else if (a.hd % 4 == 0) {
         if (o < a.hd) *reinterpret_cast<f32x4*>(dst + row * a.hd + o) = v;
       } else {
 #pragma unroll
@@ -261,8 +281,10 @@ struct RawZ<true> {
   }
 };
 
-// grid (n_q rows, parts), 4 waves that share one query row and take every
-// fourth tile of 16 keys of the part. Lane (n, g) holds key n of the tile.
+constexpr int kGenWaves = 4;  // 8 measured: 87 against 79 us (601 tokens, 128 channels), 88 against 82 (900, 32)
+
+// grid (rows / R, parts), 4 waves that share R query rows and take every fourth
+// tile of 16 keys of the part. Lane (n, g) holds key n of the tile.
 //  - z: the tile's 16 pair vectors are consecutive in memory; the lane loads
 //    channels 16j + 4g .. +3 of its key (one tile ahead) and the four lanes of a
 //    key form its two-pass LayerNorm statistics.
@@ -270,25 +292,29 @@ struct RawZ<true> {
 //    row n, B = z - mean as loaded; accumulator register i of lane (n, g) is then
 //    head 4i + g of key n, so each lane owns NH = ceil(H / 4) heads of one key,
 //  - and the logits, an online softmax of the lane's own keys and the weighted
-//    sum of v run in the lane, with k and v read straight from L2 in 16-byte
-//    loads and no exchange between lanes until the row's end.
+//    sum of v run in the lane, with k and v read straight from L2 (laid out for
+//    it by the projection) and no exchange between lanes until the row's end.
 // The 16 lanes' and 4 waves' states meet in LDS, in a fixed order.
 // DP: the head size padded to a multiple of 4; c_z <= 16 CT.
-// What bounds it: one row per workgroup reads k and v (1 KB a key at 4 x 32) from
-// L2 beside each key's z; a lane per key and its state in LDS, with z read three
-// times in 4-byte pieces, took 1810 us on 601 tokens of 128 channels.
-template <int NH, int DP, int CT, bool BF16>
-__global__ void __launch_bounds__(256, 2) gen_attn_kernel(GenAttnArgs a) {
+// What bounds it: 601 tokens of 128 channels (183 MB of z) take 79 us, the same
+// row pattern at the rate of a large read about 30: the row count fills the
+// chip's 512 workgroup slots 1.2 times, and per 16 keys the LayerNorm, softmax and
+// weighted sum issue about as many cycles of vector instructions as the bias
+// products take (1024). With k and v row-major, each lane's 16 bytes in a cache
+// line of their own, it took 106; with a lane per key, its state in LDS and z read
+// three times in 4-byte pieces, 1810.
+template <int NH, int DP, int CT, bool BF16, int R>
+__global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs a) {
   constexpr int kHd = 4 * NH * DP;  // padded channels of all lanes' heads
   constexpr int kQs = DP + 4;       // q row stride: the four heads read at once fall in different banks
-  __shared__ __align__(16) float s_q[4 * NH * kQs];
+  __shared__ __align__(16) float s_q[R][4 * NH * kQs];
   __shared__ __align__(16) float s_w[16 * 16 * CT];  // [j][lane][4]: A operands
-  __shared__ __align__(16) float s_o[4][16][kHd];
-  __shared__ float s_l[4][16][4 * NH];
-  __shared__ float s_m[4][4 * NH];
+  __shared__ __align__(16) float s_o[kGenWaves][16][kHd];
+  __shared__ float s_l[kGenWaves][16][4 * NH];
+  __shared__ float s_m[kGenWaves][4 * NH];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t row = blockIdx.x;
+  const int64_t row0 = (int64_t)blockIdx.x * R;
   const int part = blockIdx.y;
   const int H = a.n_heads, d = a.head_dim, hd = H * d, c_z = a.c_z;
   int64_t size, start;
@@ -304,19 +330,19 @@ __global__ void __launch_bounds__(256, 2) gen_attn_kernel(GenAttnArgs a) {
   float fm[CT];
 #pragma unroll
   for (int j = 0; j < CT; ++j) fm[j] = 16 * j < c_z ? 1.0f : 0.0f;
-  auto load_z = [&](int64_t t) {
+  auto load_z = [&](int64_t t, int r) {
     const int64_t key = min(start + 16 * t + n, end - 1);
-    const int64_t base = (row * a.n_tok + key) * c_z + 4 * g;
+    const int64_t base = (min(row0 + r, a.n_q - 1) * a.n_tok + key) * c_z + 4 * g;
 #pragma unroll
     for (int j = 0; j < CT; ++j) zr[j] = RawZ<BF16>::load(a.z, base + min(16 * j, c_z - 16));
   };
-  if (wave < n_tiles) load_z(wave);
+  if (wave < n_tiles) load_z(wave, 0);
 
-  for (int x = tid; x < 4 * NH * kQs; x += 256) {
-    const int h = x / kQs, e = x % kQs;
-    s_q[x] = h < H && e < d ? a.q[row * hd + h * d + e] : 0.0f;
+  for (int x = tid; x < R * 4 * NH * kQs; x += 64 * kGenWaves) {
+    const int r = x / (4 * NH * kQs), h = x / kQs - r * (4 * NH), e = x % kQs;
+    s_q[r][h * kQs + e] = h < H && e < d ? a.q[min(row0 + r, a.n_q - 1) * hd + h * d + e] : 0.0f;
   }
-  for (int x = tid; x < 16 * 16 * CT; x += 256) {
+  for (int x = tid; x < 16 * 16 * CT; x += 64 * kGenWaves) {
     const int l = (x >> 2) & 63, c = 16 * (x >> 8) + 4 * (l >> 4) + (x & 3), r = l & 15;
     const int h = 4 * (r & 3) + (r >> 2);
     s_w[x] = h < H && c < c_z ? a.w_b[h * c_z + c] * (a.gamma ? a.gamma[c] : 1.0f) : 0.0f;
@@ -324,139 +350,164 @@ __global__ void __launch_bounds__(256, 2) gen_attn_kernel(GenAttnArgs a) {
   __syncthreads();
 
   const float scale = 1.0f / sqrtf((float)d), inv_cz = 1.0f / (float)c_z;
-  float m[NH], l[NH];
-  f32x4 o[NH][DP / 4];
-  int head[NH];  // offset of the lane's heads (past the last: the last)
+  float m[R][NH], l[R][NH];
+  f32x4 o[R][NH][DP / 4];
+  int head[NH];  // the lane's heads (past the last: the last)
 #pragma unroll
   for (int i = 0; i < NH; ++i) {
-    m[i] = -INFINITY;
-    l[i] = 0.0f;
-    head[i] = min(4 * i + g, H - 1) * d;
+    head[i] = min(4 * i + g, H - 1);
 #pragma unroll
-    for (int c = 0; c < DP / 4; ++c) o[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < R; ++r) {
+      m[r][i] = -INFINITY;
+      l[r][i] = 0.0f;
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c) o[r][i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
 
-  for (int64_t t = wave; t < n_tiles; t += 4) {
+  for (int64_t t = wave; t < n_tiles; t += kGenWaves) {
     const int64_t key = start + 16 * t + n;
     const int64_t kk = min(key, end - 1);
     const bool valid = key < end && (!a.mask || a.mask[kk] != 0);
-    const float *kp = a.k + kk * hd, *vp = a.v + kk * hd;
+    int64_t at[NH];
+    int step[NH];
+#pragma unroll
+    for (int i = 0; i < NH; ++i) at[i] = kv_tile_offset(kk, a.n_tok, head[i], H, d, &step[i]);
     // k of this tile, requested before the work on z
     f32x4 kr[NH][DP / 4], vr[NH][DP / 4];
 #pragma unroll
     for (int i = 0; i < NH; ++i)
 #pragma unroll
-      for (int c = 0; c < DP / 4; ++c) kr[i][c] = *reinterpret_cast<const f32x4*>(kp + head[i] + min(4 * c, d - 4));
-    f32x4 z[CT];
+      for (int c = 0; c < DP / 4; ++c) kr[i][c] = *reinterpret_cast<const f32x4*>(a.k + at[i] + min(c, d / 4 - 1) * step[i]);
 #pragma unroll
-    for (int j = 0; j < CT; ++j) z[j] = RawZ<BF16>::to_f32(zr[j]);
-    load_z(min(t + 4, n_tiles - 1));
-    float s = 0.0f, v = 0.0f;
+    for (int r = 0; r < R; ++r) {
+      f32x4 z[CT];
 #pragma unroll
-    for (int j = 0; j < CT; ++j)
+      for (int j = 0; j < CT; ++j) z[j] = RawZ<BF16>::to_f32(zr[j]);
+      if (r + 1 < R)
+        load_z(t, r + 1);
+      else
+        load_z(min(t + kGenWaves, n_tiles - 1), 0);
+      float s = 0.0f, v = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s = fmaf(z[j][i], fm[j], s);
-    const float mu = sum4(s) * inv_cz;
+      for (int j = 0; j < CT; ++j)
 #pragma unroll
-    for (int j = 0; j < CT; ++j)
+        for (int i = 0; i < 4; ++i) s = fmaf(z[j][i], fm[j], s);
+      const float mu = sum4(s) * inv_cz;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        z[j][i] = fmaf(z[j][i], fm[j], -mu * fm[j]);
-        v = fmaf(z[j][i], z[j][i], v);
+      for (int j = 0; j < CT; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          z[j][i] = fmaf(z[j][i], fm[j], -mu * fm[j]);
+          v = fmaf(z[j][i], z[j][i], v);
+        }
+      const float rstd = 1.0f / sqrtf(fmaf(sum4(v), inv_cz, a.eps));
+      f32x4 b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < CT; ++j) {
+        const f32x4 w = *reinterpret_cast<const f32x4*>(&s_w[(j * 64 + lane) * 4]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b = mfma4(w[i], z[j][i], b);
       }
-    const float rstd = 1.0f / sqrtf(fmaf(sum4(v), inv_cz, a.eps));
-    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+      if (r == 0)
 #pragma unroll
-    for (int j = 0; j < CT; ++j) {
-      const f32x4 w = *reinterpret_cast<const f32x4*>(&s_w[(j * 64 + lane) * 4]);
+        for (int i = 0; i < NH; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) b = mfma4(w[i], z[j][i], b);
-    }
+        for (int c = 0; c < DP / 4; ++c) vr[i][c] = *reinterpret_cast<const f32x4*>(a.v + at[i] + min(c, d / 4 - 1) * step[i]);
 #pragma unroll
-    for (int i = 0; i < NH; ++i)
+      for (int i = 0; i < NH; ++i) {
+        float dot = 0.0f;
 #pragma unroll
-      for (int c = 0; c < DP / 4; ++c) vr[i][c] = *reinterpret_cast<const f32x4*>(vp + head[i] + min(4 * c, d - 4));
+        for (int c = 0; c < DP / 4; ++c) {
+          const f32x4 q = *reinterpret_cast<const f32x4*>(&s_q[r][(4 * i + g) * kQs + 4 * c]);
 #pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      float dot = 0.0f;
+          for (int e = 0; e < 4; ++e) dot = fmaf(q[e], kr[i][c][e], dot);
+        }
+        const float lg = valid ? fmaf(b[i], rstd, dot * scale) : -INFINITY;
+        const float mn = fmaxf(m[r][i], lg);
+        const float base = mn == -INFINITY ? 0.0f : mn;
+        const float al = expf(m[r][i] - base);  // 0 when m = -inf
+        const float p = expf(lg - base);     // 0 for a masked key, whose v the projection zeroed
+        l[r][i] = fmaf(l[r][i], al, p);
 #pragma unroll
-      for (int c = 0; c < DP / 4; ++c) {
-        const f32x4 q = *reinterpret_cast<const f32x4*>(&s_q[(4 * i + g) * kQs + 4 * c]);
+        for (int c = 0; c < DP / 4; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dot = fmaf(q[e], kr[i][c][e], dot);
+          for (int e = 0; e < 4; ++e) o[r][i][c][e] = fmaf(p, vr[i][c][e], o[r][i][c][e] * al);
+        m[r][i] = mn;
       }
-      const float lg = valid ? fmaf(b[i], rstd, dot * scale) : -INFINITY;
-      const float mn = fmaxf(m[i], lg);
-      const float base = mn == -INFINITY ? 0.0f : mn;
-      const float al = expf(m[i] - base);  // 0 when m = -inf
-      const float p = expf(lg - base);     // 0 for a masked key, whose v the projection zeroed
-      l[i] = fmaf(l[i], al, p);
-#pragma unroll
-      for (int c = 0; c < DP / 4; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[i][c][e] = fmaf(p, vr[i][c][e], o[i][c][e] * al);
-      m[i] = mn;
     }
   }
 
   // the lane's state relative to the wave's maximum, then all of them by channel
 #pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    float mx = m[i];
+  for (int r = 0; r < R; ++r) {
+    const int64_t row = row0 + r;
+    if (row >= a.n_q) break;
+    if (r > 0) __syncthreads();
 #pragma unroll
-    for (int x = 8; x >= 1; x >>= 1) mx = fmaxf(mx, __shfl_xor(mx, x, 16));
-    const float f = expf(m[i] - (mx == -INFINITY ? 0.0f : mx));
-    s_l[wave][n][4 * i + g] = l[i] * f;
-    if (n == 0) s_m[wave][4 * i + g] = mx;
+    for (int i = 0; i < NH; ++i) {
+      float mx = m[r][i];
 #pragma unroll
-    for (int c = 0; c < DP / 4; ++c)
-      *reinterpret_cast<f32x4*>(&s_o[wave][n][(4 * i + g) * DP + 4 * c]) = o[i][c] * f;
-  }
-  __syncthreads();
-  for (int x = tid; x < hd; x += 256) {
-    const int h = x / d, e = x - h * d;
-    float mx = -INFINITY;
+      for (int x = 8; x >= 1; x >>= 1) mx = fmaxf(mx, __shfl_xor(mx, x, 16));
+      const float f = expf(m[r][i] - (mx == -INFINITY ? 0.0f : mx));
+      s_l[wave][n][4 * i + g] = l[r][i] * f;
+      if (n == 0) s_m[wave][4 * i + g] = mx;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) mx = fmaxf(mx, s_m[w][h]);
-    float ls = 0.0f, acc = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = expf(s_m[w][h] - (mx == -INFINITY ? 0.0f : mx));
-      float lw = 0.0f, ow = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        lw += s_l[w][i][h];
-        ow += s_o[w][i][h * DP + e];
-      }
-      ls = fmaf(f, lw, ls);
-      acc = fmaf(f, ow, acc);
+      for (int c = 0; c < DP / 4; ++c)
+        *reinterpret_cast<f32x4*>(&s_o[wave][n][(4 * i + g) * DP + 4 * c]) = o[r][i][c] * f;
     }
-    const int64_t at = row * hd + x;
-    if (a.out) {  // one part: gate and normalise here
-      const float r = ls == 0.0f ? 0.0f : a.g[at] * (acc / ls);
-      if (a.out_bf16)
-        static_cast<__bf16*>(a.out)[at] = (__bf16)r;
-      else
-        static_cast<float*>(a.out)[at] = r;
-    } else {
-      a.acc_parts[(int64_t)part * a.n_q * hd + at] = acc;
-      if (e == 0) {
-        a.m_parts[((int64_t)part * H + h) * a.n_q + row] = mx;
-        a.l_parts[((int64_t)part * H + h) * a.n_q + row] = ls;
+    __syncthreads();
+    for (int x = tid; x < hd; x += 64 * kGenWaves) {
+      const int h = x / d, e = x - h * d;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < kGenWaves; ++w) mx = fmaxf(mx, s_m[w][h]);
+      float ls = 0.0f, acc = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kGenWaves; ++w) {
+        const float f = expf(s_m[w][h] - (mx == -INFINITY ? 0.0f : mx));
+        float lw = 0.0f, ow = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          lw += s_l[w][i][h];
+          ow += s_o[w][i][h * DP + e];
+        }
+        ls = fmaf(f, lw, ls);
+        acc = fmaf(f, ow, acc);
+      }
+      const int64_t at = row * hd + x;
+      if (a.out) {  // one part: gate and normalise here
+        const float r = ls == 0.0f ? 0.0f : a.g[at] * (acc / ls);
+        if (a.out_bf16)
+          static_cast<__bf16*>(a.out)[at] = (__bf16)r;
+        else
+          static_cast<float*>(a.out)[at] = r;
+      } else {
+        a.acc_parts[(int64_t)part * a.n_q * hd + at] = acc;
+        if (e == 0) {
+          a.m_parts[((int64_t)part * H + h) * a.n_q + row] = mx;
+          a.l_parts[((int64_t)part * H + h) * a.n_q + row] = ls;
+        }
       }
     }
   }
 }
 
+// Two rows per workgroup share each k and v load: faster where z is small beside
+// them and there are rows for it (32 channels, 900 tokens: 60 against 82 us), but
+// the second row's state does not fit the registers beside 64 or 128 channels
+// (601 tokens of 128: 109 against 79 us).
 template <int NH, int DP, bool BF16>
 void gen_attn_launch(const GenAttnArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)a.n_q, (unsigned)a.n_parts);
-  if (a.c_z <= 32)
-    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 2, BF16>), grid, dim3(256), 0, st, a);
+  const dim3 grid((unsigned)a.n_q, (unsigned)a.n_parts), block(64 * kGenWaves);
+  if (a.c_z <= 32 && a.n_q * a.n_parts >= 512)
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 2, BF16, 2>), dim3((grid.x + 1) / 2, grid.y), block, 0, st, a);
+  else if (a.c_z <= 32)
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 2, BF16, 1>), grid, block, 0, st, a);
   else if (a.c_z <= 64)
-    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 4, BF16>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 4, BF16, 1>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 8, BF16>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gen_attn_kernel<NH, DP, 8, BF16, 1>), grid, block, 0, st, a);
 }
 template <int NH, int DP>
 void gen_attn_launch(const GenAttnArgs& a, hipStream_t st) {

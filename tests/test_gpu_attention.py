@@ -60,6 +60,8 @@ def test_general_path_bf16_inputs(torch_cuda):
     (1, 16, 16, 1, 4, "f32", 1), (15, 33, 32, 3, 12, "f32", 2), (17, 128, 48, 4, 32, "f32", 3),
     (64, 64, 64, 5, 16, "f32", 1), (65, 70, 96, 8, 16, "bf16", 5), (100, 128, 112, 16, 8, "f32", 4),
     (90, 36, 128, 9, 8, "bf16", 1), (255, 128, 128, 4, 32, "f32", 3), (257, 96, 32, 4, 16, "f32", 3),
+    # two rows per workgroup (at most 32 channels, 512 rows and parts), an odd row count
+    (515, 32, 32, 4, 32, "f32", 1), (131, 32, 16, 6, 12, "bf16", 4),
     # shapes it does not take: the general kernel
     (40, 20, 24, 2, 6, "f32", 3), (33, 128, 144, 2, 64, "f32", 2), (260, 48, 40, 10, 12, "bf16", 2)])
 def test_general_path_shapes(torch_cuda, n_tok, c_s, c_z, h, d, dtype, n_kb):
