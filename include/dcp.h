@@ -112,7 +112,9 @@ size_t dcp_workspace_bytes(const dcp_shape* shape, int64_t n_q, int32_t n_key_bl
  *               block p has floor(N/P) + [p < N mod P] keys) and the blocks'
  *               partial states are merged in increasing order, as the ring
  *               steps of the paper's 2D scheme do. Any value gives the same
- *               result up to fp32 rounding order.
+ *               result up to fp32 rounding order, which lets the library fold
+ *               neighbouring blocks, or split one, into whatever partial
+ *               states the chip runs fastest.
  *   out         [n_q, H*d] out_dtype, 16-byte aligned
  *   workspace   device scratch of at least dcp_workspace_size() bytes,
  *               256-byte aligned; contents on entry are ignored.

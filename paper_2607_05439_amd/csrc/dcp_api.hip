@@ -67,22 +67,15 @@ int pick_path(const dcp_shape* sh, Path* p) {
               sh->act_dtype, sh->c_s, sh->c_z, sh->n_heads, sh->head_dim);
 }
 
-// Segments per key block for the fused kernel. A workgroup (kTileQ * 4 query
-// rows) holds a whole CU (160 KB of LDS), so workgroups run in rounds of
-// kSchedCUs, and a last round that fills only part of the chip leaves the rest
-// idle for a whole workgroup's time. The cost of a choice, in units of one
-// key streamed by one workgroup, is rounds x (keys per part + a fixed
-// per-workgroup cost) plus the partial states it adds (H (d+2) fp32 per row and
-// part, written then read by the merge: about 13 keys of z per row and part,
-// spread over the chip). The smallest segment count within 2% of the cheapest
-// is taken, so that more partials are only paid for a real gain. No part is
-// longer than kMaxPartKeys keys: each part's fp32 accumulator is one sequential
-// chain of per-tile matrix-core sums, and bounding its length bounds the
-// rounding difference between two blockings of the same keys.
+// Partial states per key block that the fused path's workspace has room for (its
+// size is part of the interface, so this rule stays as it is; fast_parts below
+// takes as many as pay). The cost of a count, in keys streamed by 64 query rows,
+// is rounds of kSchedCUs x (keys per part + a fixed cost) plus the partial states
+// it adds; the smallest within 2% of the cheapest is taken.
 constexpr int64_t kSchedCUs = 256;     // CUs of an MI350X / MI355X (gfx950)
-constexpr int64_t kMaxPartKeys = 4096;
-constexpr int64_t kGroupCostKeys = 8;  // prologue (q, weights, ring fill) and epilogue, in keys
-constexpr int64_t kPartCostKeys = 13;  // partial state per row and part, in keys of z per row
+constexpr int64_t kMaxPartKeys = 4096; // see fast_parts
+constexpr int64_t kGroupCostKeys = 8;
+constexpr int64_t kPartCostKeys = 13;
 
 int fast_segments(int64_t n_tok, int64_t n_q, int32_t n_kb) {
   const int64_t groups = (n_q + 4 * dcp::kTileQ - 1) / (4 * dcp::kTileQ);
@@ -107,9 +100,49 @@ int fast_segments(int64_t n_tok, int64_t n_q, int32_t n_kb) {
   return (int)seg_min;
 }
 
+// Parts that the fused attention splits a key range into, at most max_parts. A
+// workgroup holds 16 query rows and two fit a CU, so a launch runs in rounds of
+// 512; what a part costs, in keys at the rate of a full round (0.31 us per key of
+// 512 workgroups, 6.75 TB/s), was fitted to sweeps of the part count on 200 to 24000
+// tokens: a full round its keys; a last, partial round r workgroups' share of
+// the stream, but at least 0.45 of a round's time per key alone on a CU and 0.87
+// with two on some; each round 51 keys for its start and end; and each partial
+// state 0.0021 per row for writing and merging it. 1024 tokens: 54 us at 4 or 8
+// parts (256 or 512 workgroups), 65 at 16, 69 at 5; 4800 tokens: 922 us at 5, 1007
+// at 10; 3000 rows of 12000: 1363 us at 4, 1400 at 8, 1693 at 3.
+// No part is longer than kMaxPartKeys keys where max_parts allows it: each part's
+// fp32 accumulator is one sequential chain of per-tile matrix-core sums, and
+// bounding its length bounds the rounding difference between two partitions of
+// the same keys.
+int fast_parts(int64_t k_lo, int64_t k_len, int64_t n_q, int64_t max_parts) {
+  const int64_t groups = (n_q + dcp::kTileQ - 1) / dcp::kTileQ;
+  const int64_t tiles = ((k_lo + k_len + dcp::kTileK - 1) / dcp::kTileK) - k_lo / dcp::kTileK;
+  int64_t cap = max_parts < tiles ? max_parts : tiles;
+  if (cap > 1024) cap = 1024;
+  int64_t first = (k_len + kMaxPartKeys - 1) / kMaxPartKeys;
+  if (first > cap) first = cap;
+  if (first < 1) first = 1;
+  int64_t pick = first;
+  double best = 0.0;
+  for (int64_t p = first; p <= cap; ++p) {
+    const double keys = (double)(dcp::kTileK * ((tiles + p - 1) / p));
+    const int64_t full = groups * p / 512, r = groups * p % 512;
+    double cost = (double)full * (keys + 51.0) + 0.0021 * (double)(n_q * p);
+    if (r > 0) {
+      const double alone = r <= 256 ? 0.45 : 0.87, share = (double)r / 512.0;
+      cost += keys * (alone > share ? alone : share) + 51.0;
+    }
+    if (p == first || cost < best) {
+      best = cost;
+      pick = p;
+    }
+  }
+  return (int)pick;
+}
+
 struct Layout {
   Path path;
-  int n_seg, n_parts;
+  int n_parts;
   int64_t nq_pad, n_pad;
   size_t off_q, off_k, off_v, off_tv, off_ws, off_g, off_m, off_l, off_acc, total;
 };
@@ -124,8 +157,7 @@ void make_layout(const dcp_shape* sh, Path path, int64_t n_q, int32_t n_kb, Layo
     return o;
   };
   if (path == kPathFast) {
-    L->n_seg = fast_segments(sh->n_tokens, n_q, n_kb);
-    L->n_parts = n_kb * L->n_seg;
+    L->n_parts = n_kb * fast_segments(sh->n_tokens, n_q, n_kb);
     L->nq_pad = (n_q + 15) / 16 * 16;
     L->n_pad = (sh->n_tokens + 15) / 16 * 16;
     L->off_q = take((size_t)dcp::kFastH * L->nq_pad * dcp::kFastDp * 2);
@@ -134,7 +166,6 @@ void make_layout(const dcp_shape* sh, Path path, int64_t n_q, int32_t n_kb, Layo
     L->off_tv = take((size_t)(L->n_pad / 16) * 4);
     L->off_ws = take(dcp::fast_proj_split_bytes(sh->c_s));
   } else {
-    L->n_seg = 1;
     L->n_parts = n_kb;
     L->nq_pad = n_q;
     L->n_pad = sh->n_tokens;
@@ -196,13 +227,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     return fail(DCP_ERR_INVALID_ARGUMENT, "w_q, w_k, w_v, w_g, w_b and ln_gamma must be 16-byte aligned");
   Layout L;
   make_layout(shape, path, n_q, n_key_blocks, &L);
-  // a key range shorter than N: its own segment count, never more parts than
-  // the layout holds, so the same workspace serves
-  if (path == kPathFast && k_len < shape->n_tokens) {
-    const int seg = fast_segments(k_len > 0 ? k_len : 1, n_q, n_key_blocks);
-    if (seg < L.n_seg) L.n_seg = seg;
-    L.n_parts = n_key_blocks * L.n_seg;
-  }
+  if (path == kPathFast && k_len > 0) L.n_parts = fast_parts(k_lo, k_len, n_q, L.n_parts);
   if (!workspace || !aligned(workspace, 256))
     return fail(DCP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
   if (workspace_bytes < L.total)
@@ -253,8 +278,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     aa.n_pad = L.n_pad;
     aa.k_lo = k_lo;
     aa.k_len = k_len;
-    aa.n_kb = n_key_blocks;
-    aa.n_seg = L.n_seg;
+    aa.n_parts = L.n_parts;
     aa.eps = shape->ln_eps;
     aa.m_parts = reinterpret_cast<float*>(ws + L.off_m);
     aa.l_parts = reinterpret_cast<float*>(ws + L.off_l);

@@ -37,20 +37,6 @@ __host__ __device__ inline void chunk_of(int64_t total, int64_t parts, int64_t p
   *start = p * q + (p < r ? p : r);
 }
 
-// Key range of internal part `part` = (block b, segment s): the keys are split
-// into n_kb blocks by the chunk rule, and each block into n_seg segments by the
-// same rule. Parts are ordered block-major, so merging them in index order
-// merges the blocks in increasing order.
-__host__ __device__ inline void part_range(int64_t n_tok, int n_kb, int n_seg, int part, int64_t* start,
-                                           int64_t* end) {
-  const int b = part / n_seg, s = part % n_seg;
-  int64_t bs, b0, ss, s0;
-  chunk_of(n_tok, n_kb, b, &bs, &b0);
-  chunk_of(bs, n_seg, s, &ss, &s0);
-  *start = b0 + s0;
-  *end = b0 + s0 + ss;
-}
-
 struct FastProjArgs {
   const uint16_t* s;  // [N, c_s] bf16
   const float *w_q, *w_k, *w_v, *w_g;
@@ -72,11 +58,10 @@ struct FastAttnArgs {
   const uint16_t *q, *k, *vt;
   const uint32_t* tile_valid;
   int64_t n_tok, n_q, nq_pad, n_pad;
-  int64_t k_lo, k_len;  // keys [k_lo, k_lo + k_len), split into n_kb blocks x n_seg segments
-  int32_t n_kb, n_seg;
+  int64_t k_lo, k_len;  // keys [k_lo, k_lo + k_len), split into n_parts parts of whole 16-key tiles
+  int32_t n_parts;
   float eps;
   float *m_parts, *l_parts, *acc_parts;  // [P][H][n_q], [P][H][n_q], [P][n_q][H][d]
-  int32_t xcd_order;                     // set by the launcher: workgroup numbering (attn_kernel)
 };
 
 struct FastBiasArgs {

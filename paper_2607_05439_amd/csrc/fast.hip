@@ -1,11 +1,10 @@
 // Fused bf16 path for c_z = 128, H = 16, d = 24 on gfx950 (CDNA4).
 //
 // Kernels (the q, k, v, g projections that feed them are in proj.hip):
-//   attn_kernel  the hot loop: one wave owns 16 query rows and one key range
-//                (a ring step of the paper's 2D scheme, or a slice of one). Per
-//                key it reads the 16 rows' pair vectors z[i, j, :] once from
-//                HBM, forms LayerNorm statistics and the c_z -> H bias
-//                projection on the matrix cores, then per 16-key tile runs
+//   attn_kernel  the hot loop: a workgroup owns 16 query rows and one key range
+//                (a part). Per key it reads the 16 rows' pair vectors z[i, j, :]
+//                once from HBM, forms LayerNorm statistics and the c_z -> H
+//                bias projection on the matrix cores, then per 16-key tile runs
 //                QK^T and PV on the matrix cores with an fp32 online softmax.
 //                It writes one partial state (m, l, acc) per (row, head).
 //   bias_ring_kernel  the pair bias alone, materialised (dcp_bias_project):
@@ -31,7 +30,6 @@ namespace dcp {
 namespace {
 
 constexpr int kCz = kFastCz, kH = kFastH, kD = kFastD, kDp = kFastDp;
-constexpr int kPre = 4;  // keys of z in flight per wave (registers)
 constexpr float kLog2e = 1.44269504088896340736f;
 // Logits in base-2 units are offset by this constant inside the QK^T
 // accumulator, so every logit of moderate size lands in [128, 256) and is
@@ -49,26 +47,37 @@ constexpr float kShift = kFastShift;
 // w_b and gamma are 16-byte aligned (checked on the host): each lane reads its
 // 8 consecutive channels per k-step as two 16-byte loads, and the absence of
 // gamma is one wave-uniform branch, not one per element.
-__device__ void bias_weights(const float* __restrict__ w_b, const float* __restrict__ gamma, float scale, int lane,
-                             bf16x8 (&hi)[4], bf16x8 (&lo)[4]) {
+struct BiasRaw {
+  float w[4][8], gamma[4][8];
+};
+__device__ __forceinline__ void bias_weights_load(const float* __restrict__ w_b, const float* __restrict__ gamma,
+                                                  int lane, BiasRaw& r) {
   const int h = lane & 15, g = lane >> 4;
-  float w[4][8];
   const float4* wr = reinterpret_cast<const float4*>(w_b + h * kCz + 8 * g);  // channel 32 s + 8 g + i: float4 8 s + i / 4
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     const float4 a = wr[8 * s], b = wr[8 * s + 1];
-    w[s][0] = a.x, w[s][1] = a.y, w[s][2] = a.z, w[s][3] = a.w;
-    w[s][4] = b.x, w[s][5] = b.y, w[s][6] = b.z, w[s][7] = b.w;
+    r.w[s][0] = a.x, r.w[s][1] = a.y, r.w[s][2] = a.z, r.w[s][3] = a.w;
+    r.w[s][4] = b.x, r.w[s][5] = b.y, r.w[s][6] = b.z, r.w[s][7] = b.w;
   }
   if (gamma) {
     const float4* gr = reinterpret_cast<const float4*>(gamma + 8 * g);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const float4 a = gr[8 * s], b = gr[8 * s + 1];
-      const float gm[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) w[s][i] *= gm[i];
+      r.gamma[s][0] = a.x, r.gamma[s][1] = a.y, r.gamma[s][2] = a.z, r.gamma[s][3] = a.w;
+      r.gamma[s][4] = b.x, r.gamma[s][5] = b.y, r.gamma[s][6] = b.z, r.gamma[s][7] = b.w;
     }
+  }
+}
+__device__ __forceinline__ void bias_weights_finish(BiasRaw& r, bool has_gamma, float scale, bf16x8 (&hi)[4],
+                                                    bf16x8 (&lo)[4]) {
+  auto& w = r.w;
+  if (has_gamma) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[s][i] *= r.gamma[s][i];
   }
   float rs = 0.f;
 #pragma unroll
@@ -88,6 +97,12 @@ __device__ void bias_weights(const float* __restrict__ w_b, const float* __restr
       hi[s][i] = x;
       lo[s][i] = (__bf16)(c - (float)x);
     }
+}
+__device__ __forceinline__ void bias_weights(const float* __restrict__ w_b, const float* __restrict__ gamma,
+                                             float scale, int lane, bf16x8 (&hi)[4], bf16x8 (&lo)[4]) {
+  BiasRaw r;
+  bias_weights_load(w_b, gamma, lane, r);
+  bias_weights_finish(r, gamma != nullptr, scale, hi, lo);
 }
 
 // One key for the wave's 16 rows: z B operands (k-step s = channels 32s+8g..+7
@@ -153,24 +168,13 @@ __device__ __forceinline__ f32x4 bias_weight_sums(const bf16x8 (&whi)[4], const 
 }
 
 // ----------------------------------------------------------------------------- attention
-constexpr int kWaves = 4;           // waves per workgroup: 4 query tiles sharing one key range
-constexpr int kRing = 8;            // z slots per wave (LDS ring)
-constexpr int kAhead = kRing - 1;   // keys of z in flight ahead of the one being used
-constexpr int kKvDma = 8;           // DMA loads per wave per K/V tile (4 heads x K, V)
+constexpr int kWaves = 4;  // waves per workgroup, sharing 16 query rows and one key range
 
 // One key's z for a wave's 16 rows: [row][16-byte chunk], chunk index XOR row
 // (so the 16 rows of one operand read hit 16 different bank groups).
 struct ZSlot {
   u32x4 c[16][16];
 };
-// K and V^T of one 16-key tile for all heads, in matrix-core operand order:
-// k[h][L] = lane L's QK^T A operand; v[h][L] = lane L's PV A operands (M-tile 0
-// in .xy, M-tile 1 in .zw).
-struct KvTile {
-  u32x4 k[kH][64];
-  u32x4 v[kH][64];
-};
-
 typedef const __attribute__((address_space(4))) uint32_t* const_u32_ptr;
 
 // Valid keys of tile t: the per-tile key mask, restricted to [start, end). The
@@ -183,239 +187,269 @@ __device__ __forceinline__ uint32_t tile_valid_bits(const_u32_ptr tv, int64_t t,
   return tv[t] & range;
 }
 
-// Outstanding DMA loads allowed when waiting for key kk of a tile: the z loads
-// of the kAhead - 1 keys issued after it, plus the K/V tile loads when those
-// were issued after it (for the first kAhead keys, whose z was issued during
-// the previous tile).
-template <int KK>
-__device__ __forceinline__ void wait_key() {
-  wait_vm<4 * (kAhead - 1) + (KK < kAhead ? kKvDma : 0)>();
+// One workgroup = 16 query rows over one key range (a part). Of each 16-key tile
+// a wave streams four keys' z through its own LDS ring, forms their bias for all
+// 16 heads and writes it to an LDS tile [head][row][key]; after one barrier it
+// runs the softmax attention of four heads over the tile's 16 keys. A wave thus
+// holds the state of 4 heads, under 256 registers and 80 KB of LDS per workgroup:
+// two workgroups fit a CU, and one wave's arithmetic hides behind the others'
+// streams. The bias comes out of LDS in the accumulator layout of QK^T.
+//
+// What bounds it: the z stream. A 3000-row stripe of 12000 tokens runs at 6.75
+// TB/s (1365 us), the rate of the same loads without arithmetic. The form
+// before it (a wave held all 16 heads of 16 rows, 490 registers and 160 KB of LDS,
+// one wave per SIMD) took 1510 us there, 67 us on 1024 tokens (54 now) and 50 us on
+// 333 (19.5 now), with the same bits over the same parts.
+//
+// k and v go straight from L2 to registers, one tile ahead, as ordinary loads
+// whose waits the compiler counts; for its counts to be exact the z copies into
+// LDS are builtins it sees, and every access to LDS in the loop is inline asm,
+// because it would wait for all outstanding copies before an LDS access of its
+// own. The waits for z are explicit.
+constexpr int kRing = 3;  // z slots per wave: a slot is refilled as soon as its key is in registers
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+// One key of the z stream into the LDS slot at `lds` (dma_key_stream's four loads).
+__device__ __forceinline__ void dma_key_counted(__amdgpu_buffer_rsrc_t r, int v0, int v1, int v2, int v3, uint32_t lds) {
+  lds_ptr p = (lds_ptr)(uintptr_t)lds;
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, p, 16, v0, 0, 0, 2);  // aux 2: non-temporal
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, p, 16, v1, 0, 1024, 2);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, p, 16, v2, 0, 2048, 2);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, p, 16, v3, 0, 3072, 2);
 }
 
-// One workgroup = 4 waves = 4 tiles of 16 query rows over the same key range
-// (one internal part). Each wave streams its rows' z through its own LDS ring
-// with direct-to-LDS loads issued kAhead keys ahead; an invalid (masked or
-// out-of-range) key gets an out-of-range offset, so its load moves no data and
-// every load is unconditional. K/V tiles are loaded into LDS one tile ahead,
-// each wave fetching 4 heads, into one LDS buffer; two barriers per tile (the
-// second, after the compute-only attention phase, frees the buffer).
-__global__ void __launch_bounds__(256, 1) attn_kernel(FastAttnArgs a) {
-  __shared__ ZSlot zring[kWaves][kRing];  // 128 KB
-  __shared__ KvTile kv;                   // 32 KB
+// Wait until at most N loads are outstanding, then four 16-byte LDS reads.
+template <int N>
+__device__ __forceinline__ void read_key(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4 (&z)[4]) {
+  asm volatile(
+      "s_waitcnt vmcnt(%8)\n\t"
+      "ds_read_b128 %0, %4\n\t"
+      "ds_read_b128 %1, %5\n\t"
+      "ds_read_b128 %2, %6\n\t"
+      "ds_read_b128 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(z[0]), "=&v"(z[1]), "=&v"(z[2]), "=&v"(z[3])
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "n"(N)
+      : "memory");
+}
+// Rows of the bias tile 1 KB apart: four reads, four writes.
+__device__ __forceinline__ void read_bias4(uint32_t at, f32x4 (&b)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\t"
+      "ds_read_b128 %1, %4 offset:1024\n\t"
+      "ds_read_b128 %2, %4 offset:2048\n\t"
+      "ds_read_b128 %3, %4 offset:3072\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
+      : "v"(at)
+      : "memory");
+}
+__device__ __forceinline__ void write_bias4(uint32_t at, f32x4 b0, f32x4 b1, f32x4 b2, f32x4 b3) {
+  asm volatile(
+      "ds_write_b128 %0, %1\n\t"
+      "ds_write_b128 %0, %2 offset:1024\n\t"
+      "ds_write_b128 %0, %3 offset:2048\n\t"
+      "ds_write_b128 %0, %4 offset:3072"
+      :
+      : "v"(at), "v"(b0), "v"(b1), "v"(b2), "v"(b3)
+      : "memory");
+}
+
+// Tiles [t_begin, t_end) of part p: the range's 16-key tiles split by the chunk
+// rule (no tile belongs to two parts; none is empty while parts <= tiles).
+__device__ __forceinline__ void part_tiles(int64_t k_lo, int64_t k_len, int parts, int p, int64_t* t_begin,
+                                                 int64_t* t_end) {
+  const int64_t t0 = k_lo >> 4, t1 = (k_lo + k_len + 15) >> 4;
+  int64_t size, first;
+  chunk_of(t1 - t0, parts, p, &size, &first);
+  *t_begin = t0 + first;
+  *t_end = t0 + first + size;
+}
+
+__global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
+  __shared__ ZSlot zring[kWaves][kRing];      // 48 KB
+  __shared__ f32x4 btile[2][kH][kTileQ][4];        // 32 KB: [buffer][head][row][4 keys, chunk ^ row / 4]
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t n_qt = a.nq_pad / kTileQ;
-  // Workgroup -> (row group, part). The hardware deals workgroups to the 8
-  // XCDs in turn (workgroup i to XCD i % 8). By default row groups vary
-  // fastest, so the resident workgroups of every XCD stream the same part.
-  // With xcd_order (layers of at least 256 row groups), XCD x takes the row
-  // groups rg = x (mod 8), all parts of them, one part after another starting
-  // at part x mod P: each XCD's L2 still serves one part's K/V at a time while
-  // the XCDs stream z at different key positions.
-  int64_t rg;
-  int part;
-  if (a.xcd_order) {
-    const int P = a.n_kb * a.n_seg;
-    const int64_t n_rg = (n_qt + kWaves - 1) / kWaves;
-    const int x = blockIdx.x & 7;
-    const int64_t k = blockIdx.x >> 3;
-    const int64_t cnt = (n_rg - x + 7) / 8;  // row groups of this XCD
-    if (k >= cnt * P) return;                // whole workgroup, before any barrier
-    rg = x + 8 * (k % cnt);
-    part = (int)((x + k / cnt) % P);
-  } else {
-    rg = blockIdx.x;
-    part = blockIdx.y;
-  }
-  const int64_t qt = rg * kWaves + wave;
-  const bool active = qt < n_qt;
-  const int64_t q0 = (active ? qt : n_qt - 1) * kTileQ;
+  const int part = blockIdx.y;
+  const int64_t q0 = (int64_t)blockIdx.x * kTileQ;
   int64_t start, end;
-  part_range(a.k_len, a.n_kb, a.n_seg, part, &start, &end);
-  start += a.k_lo;
-  end += a.k_lo;
-  const int64_t t_begin = start >> 4, t_end = (end + 15) >> 4;
-  const int64_t n_tiles_all = a.n_pad / 16;
+  int64_t t_begin, t_end;
+  part_tiles(a.k_lo, a.k_len, a.n_parts, part, &t_begin, &t_end);
+  start = max(a.k_lo, 16 * t_begin);
+  end = min(a.k_lo + a.k_len, 16 * t_end);
+  const int n_tiles_all = (int)(a.n_pad / 16);
 
-  bf16x8 whi[4], wlo[4];
-  bias_weights(a.w_b, a.gamma, kLog2e, lane, whi, wlo);
-  const f32x4 wsum = bias_weight_sums(whi, wlo);
-  bf16x8 qreg[kH];
+  BiasRaw braw;
+  bias_weights_load(a.w_b, a.gamma, lane, braw);
+  constexpr int kHw = kH / kWaves;  // heads of this wave: kHw * wave ..
+  bf16x8 qreg[kHw];
 #pragma unroll
-  for (int h = 0; h < kH; ++h)
-    qreg[h] = as_bf16x8(*(reinterpret_cast<const u32x4*>(a.q) + ((int64_t)h * a.nq_pad + q0 + n) * 4 + g));
+  for (int j = 0; j < kHw; ++j)
+    qreg[j] = as_bf16x8(
+        *(reinterpret_cast<const u32x4*>(a.q) + ((int64_t)(kHw * wave + j) * a.nq_pad + q0 + n) * 4 + g));
 
-  float m[kH];
-  f32x4 o[kH][2];
-#pragma unroll
-  for (int h = 0; h < kH; ++h) {
-    m[h] = -INFINITY;
-    o[h][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-    o[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  // z rows q0 .. q0+15 of this wave: one buffer resource, 32-bit byte offsets.
+  // z rows q0 .. q0+15: one buffer resource, 32-bit byte offsets. Load i of a key
+  // fills slot rows 4i..4i+3; lane L writes row 4i + L/16, physical chunk L%16,
+  // which holds logical chunk (L%16) ^ row. The instruction offset 1024 i, which
+  // moves the LDS and the global address alike, selects the slot's quarter, so
+  // load i's vector offset is that of its rows minus 1024 i. An invalid key
+  // (masked, or outside the part) gets an out-of-range offset: its load moves no
+  // data, so every load is unconditional.
   const int64_t rows_here = min((int64_t)kTileQ, a.n_q - q0);
   const int row_bytes = (int)(a.n_tok * (kCz * 2));
   const __amdgpu_buffer_rsrc_t zres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(a.z) + q0 * a.n_tok * kCz, 0, (int)(rows_here * row_bytes), kRawBufferFlags);
-  // DMA instruction i of a key fills slot rows 4i..4i+3; lane L writes row
-  // 4i + L/16, physical chunk L%16, which holds logical chunk (L%16) ^ row.
   int zoff[4];
+  uint32_t zread[4];
+  const uint32_t ring_base = lds_addr(&zring[wave][0]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = 4 * i + (lane >> 4);
-    zoff[i] = row * row_bytes + 16 * ((lane & 15) ^ row);
+    zoff[i] = row * row_bytes + 16 * ((lane & 15) ^ row) - 1024 * i;
+    zread[i] = ring_base + 256 * n + 16 * ((4 * i + g) ^ n);
   }
-  const uint32_t ring_base = lds_addr(&zring[wave][0]);
-  // one M0 per key: the instruction offset 1024 i, which moves the LDS and the
-  // global address alike, selects load i's quarter of the slot, so its vector
-  // offset is that of its rows minus 1024 i
-#pragma unroll
-  for (int i = 0; i < 4; ++i) zoff[i] -= 1024 * i;
-  auto z_dma = [&](int64_t j, bool valid, int slot) {
-    const int jo = (int)j * (kCz * 2);
-    dma_key_stream(zres, valid ? zoff[0] + jo : kOutOfRange, valid ? zoff[1] + jo : kOutOfRange,
-                   valid ? zoff[2] + jo : kOutOfRange, valid ? zoff[3] + jo : kOutOfRange,
-                   ring_base + (uint32_t)slot * (uint32_t)sizeof(ZSlot));
+  const const_u32_ptr tv = (const_u32_ptr)(a.tile_valid);
+  uint32_t bits = tile_valid_bits(tv, t_begin, start, end);
+  auto z_dma = [&](int64_t t, uint32_t tile_bits, int kk, uint32_t slot) {
+    const int k = kWaves * wave + kk;  // kWaves = 4 keys of each tile per wave
+    const bool valid = (tile_bits >> k) & 1u;
+    const int jo = (int)(t * 16 + k) * (kCz * 2);
+    dma_key_counted(zres, valid ? zoff[0] + jo : kOutOfRange, valid ? zoff[1] + jo : kOutOfRange,
+                    valid ? zoff[2] + jo : kOutOfRange, valid ? zoff[3] + jo : kOutOfRange,
+                    ring_base + slot * (uint32_t)sizeof(ZSlot));
   };
-  // K/V tiles: this wave fetches heads 4*wave .. 4*wave+3.
   const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(a.k), 0, (int)(kH * a.n_pad * kDp * 2), kRawBufferFlags);
   const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(a.vt), 0, (int)(kH * a.n_pad * kDp * 2), kRawBufferFlags);
-  auto kv_dma = [&](int64_t t) {
-    const uint32_t base = lds_addr(&kv);
+  u32x4 kt[kHw], vt[kHw];
+  auto kv_load = [&](int64_t t) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int h = 4 * wave + i;
-      dma_b128(kres, (int)((((int64_t)h * a.n_pad + t * 16 + n) * kDp + 8 * g) * 2),
-               base + (uint32_t)offsetof(KvTile, k) + (uint32_t)(h * 64 * 16));
-      dma_b128(vres, (int)((((int64_t)h * n_tiles_all + t) * 64 + lane) * 16),
-               base + (uint32_t)offsetof(KvTile, v) + (uint32_t)(h * 64 * 16));
+    for (int j = 0; j < kHw; ++j) {
+      const int so = ((kHw * wave + j) * n_tiles_all + (int)t) * 1024;  // 1 KB per head and tile
+      kt[j] = __builtin_amdgcn_raw_buffer_load_b128(kres, 64 * n + 16 * g, so, 0);
+      vt[j] = __builtin_amdgcn_raw_buffer_load_b128(vres, 16 * lane, so, 0);
     }
+    asm volatile("" ::: "memory");
   };
 
-  const const_u32_ptr tvres = (const_u32_ptr)(a.tile_valid);
-  uint32_t bits = t_begin < t_end ? tile_valid_bits(tvres, t_begin, start, end) : 0u;
-  if (t_begin < t_end) {
-    // same issue order as the steady state: the first kAhead keys, then K/V
+  asm volatile("" ::: "memory");
+  uint32_t slot = 0;
 #pragma unroll
-    for (int p = 0; p < kAhead; ++p) z_dma(t_begin * 16 + p, (bits >> p) & 1u, (int)((t_begin * 16 + p) % kRing));
-    kv_dma(t_begin);
+  for (int p = 0; p < kRing; ++p) z_dma(t_begin, bits, p, p);
+  kv_load(t_begin);
+
+  bf16x8 whi[4], wlo[4];
+  bias_weights_finish(braw, a.gamma != nullptr, kLog2e, whi, wlo);
+  const f32x4 wsum = bias_weight_sums(whi, wlo);
+  float m[kHw];
+  f32x4 o[kHw][2];
+#pragma unroll
+  for (int j = 0; j < kHw; ++j) {
+    m[j] = -INFINITY;
+    o[j][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    o[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  const uint32_t b_write = lds_addr(&btile[0][4 * g][n][wave ^ (n >> 2)]);
+  const uint32_t b_read = lds_addr(&btile[0][kHw * wave][n][g ^ (n >> 2)]);
+  uint32_t buf = 0;
 
   for (int64_t t = t_begin; t < t_end; ++t) {
-    const uint32_t bits_next = (t + 1 < t_end) ? tile_valid_bits(tvres, t + 1, start, end) : 0u;
-    const int slot0 = (int)((t * 16) % kRing);
-    float b[16][4];
+    const uint32_t bits_next = (t + 1 < t_end) ? tile_valid_bits(tv, t + 1, start, end) : 0u;
+    f32x4 b[4];  // [head 4g + i] over the wave's four keys
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      int slot = slot0 + kk % kRing;
-      if (slot >= kRing) slot -= kRing;
-      if (kk < kAhead)
-        wait_key<0>();
+    for (int kk = 0; kk < 4; ++kk) {
+      // loads younger than this key's: those of the next two keys, and the tile's
+      // k and v when they were issued after it (the first three keys)
+      const uint32_t so = slot * (uint32_t)sizeof(ZSlot);
+      u32x4 zb[4];
+      if (kk < kRing)
+        read_key<4 * (kRing - 1) + 2 * kHw>(zread[0] + so, zread[1] + so, zread[2] + so, zread[3] + so, zb);
       else
-        wait_key<kAhead>();
-      if ((bits >> kk) & 1u) {
-        const ZSlot& zs = zring[wave][slot];
-        u32x4 zb[4];
-#pragma unroll
-        for (int st = 0; st < 4; ++st) zb[st] = zs.c[n][(4 * st + g) ^ n];
+        read_key<4 * (kRing - 1)>(zread[0] + so, zread[1] + so, zread[2] + so, zread[3] + so, zb);
+      if (kk + kRing < 4)
+        z_dma(t, bits, kk + kRing, slot);
+      else
+        z_dma(t + 1, bits_next, kk + kRing - 4, slot);
+      slot = slot == kRing - 1 ? 0 : slot + 1;
+      if ((bits >> (kWaves * wave + kk)) & 1u) {
         f32x4 acc;
         float rstd;
         pair_bias(zb, whi, wlo, wsum, a.eps, n, acc, rstd);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[kk][i] = fmaf(acc[i], rstd, kShift);
+        for (int i = 0; i < 4; ++i) b[i][kk] = fmaf(acc[i], rstd, kShift);
       } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[kk][i] = -INFINITY;
+        for (int i = 0; i < 4; ++i) b[i][kk] = -INFINITY;
       }
-      const int nk = kk + kAhead;
-      int nslot = slot + kAhead;
-      if (nslot >= kRing) nslot -= kRing;
-      if (nk < 16)
-        z_dma(t * 16 + nk, (bits >> nk) & 1u, nslot);
-      else
-        z_dma((t + 1) * 16 + (nk - 16), (bits_next >> (nk - 16)) & 1u, nslot);
     }
-    // K/V tile t is complete in this wave (its loads precede the last key's);
-    // after the barrier, in every wave.
+    write_bias4(b_write + buf, b[0], b[1], b[2], b[3]);
+    // one barrier per tile: the other buffer is written next, and no wave gets
+    // back to this one before every wave has passed the next barrier, after
+    // its reads below
     barrier_lds();
-    const KvTile& cur = kv;
-    transpose_bias(b);
-
-    // heads in pairs: two independent QK^T / softmax chains and one vote per
-    // pair on rescaling (a factor of exactly 1 leaves a head unchanged)
-    constexpr int kG = 2;
+    f32x4 cin[kHw];
+    read_bias4(b_read + buf, cin);
+    buf ^= (uint32_t)sizeof(btile[0]);
 #pragma unroll
-    for (int h0 = 0; h0 < kH; h0 += kG) {
-      f32x4 x[kG];
-      float mnew[kG], muse[kG], alpha[kG];
+    for (int h0 = 0; h0 < kHw; h0 += 2) {
+      f32x4 x[2];
+      float mnew[2], muse[2], alpha[2];
 #pragma unroll
-      for (int j = 0; j < kG; ++j) {
-        const int h = h0 + j, ha = h >> 2, hi = h & 3;
-        const f32x4 cin = {b[4 * ha + 0][hi], b[4 * ha + 1][hi], b[4 * ha + 2][hi], b[4 * ha + 3][hi]};
-        const u32x4 kt = cur.k[h][lane];
-        // x[r]: logit (base 2, + kShift) of row n, key 4g + r
-        x[j] = mfma32(as_bf16x8(kt), qreg[h], cin);
-      }
+      for (int j = 0; j < 2; ++j) x[j] = mfma32(as_bf16x8(kt[h0 + j]), qreg[h0 + j], cin[h0 + j]);
 #pragma unroll
-      for (int j = 0; j < kG; ++j) {
-        const int h = h0 + j;
+      for (int j = 0; j < 2; ++j) {
         const float tmax = max4(fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])));
-        mnew[j] = fmaxf(m[h], ceilf(tmax));
+        mnew[j] = fmaxf(m[h0 + j], ceilf(tmax));
         muse[j] = (mnew[j] == -INFINITY) ? 0.0f : mnew[j];
-        alpha[j] = (m[h] == -INFINITY) ? 0.0f : ldexpf(1.0f, (int)(m[h] - muse[j]));
+        alpha[j] = (m[h0 + j] == -INFINITY) ? 0.0f : ldexpf(1.0f, (int)(m[h0 + j] - muse[j]));
       }
-      bf16x4 p[kG];
+      bf16x4 p[2];
 #pragma unroll
-      for (int j = 0; j < kG; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[j][r] = (__bf16)__builtin_amdgcn_exp2f(x[j][r] - muse[j]);
-      // the running maximum is an integer and rarely moves, so most pairs skip this
       bool mv = false;
 #pragma unroll
-      for (int j = 0; j < kG; ++j) mv = mv || alpha[j] != 1.0f;
+      for (int j = 0; j < 2; ++j) mv = mv || alpha[j] != 1.0f;
       if (__any(mv)) {
 #pragma unroll
-        for (int j = 0; j < kG; ++j) {
+        for (int j = 0; j < 2; ++j) {
           o[h0 + j][0] *= alpha[j];
           o[h0 + j][1] *= alpha[j];
         }
       }
 #pragma unroll
-      for (int j = 0; j < kG; ++j) {
-        const int h = h0 + j;
-        const u32x4 vv = cur.v[h][lane];
-        o[h][0] = mfma16(as_bf16x4(u32x2{vv[0], vv[1]}), p[j], o[h][0]);
-        o[h][1] = mfma16(as_bf16x4(u32x2{vv[2], vv[3]}), p[j], o[h][1]);
-        m[h] = mnew[j];
+      for (int j = 0; j < 2; ++j) {
+        const u32x4 vv = vt[h0 + j];
+        o[h0 + j][0] = mfma16(as_bf16x4(u32x2{vv[0], vv[1]}), p[j], o[h0 + j][0]);
+        o[h0 + j][1] = mfma16(as_bf16x4(u32x2{vv[2], vv[3]}), p[j], o[h0 + j][1]);
+        m[h0 + j] = mnew[j];
       }
     }
-    // every wave is done with K/V tile t: load tile t+1 into the same buffer
-    barrier_lds();
-    if (t + 1 < t_end) kv_dma(t + 1);
+    asm volatile("" ::: "memory");
+    kv_load(min(t + 1, t_end - 1));
     bits = bits_next;
   }
-  wait_vm<0>();  // the last tile's look-ahead loads (no data) before exit
+  wait_vm<0>();  // the look-ahead copies (no data) before exit
 
-  // Partial state of rows q0 + n: o[h][0][i] = acc e = 4g+i, o[h][1][i] = acc
-  // e = 16+4g+i (e = 24 is the denominator l).
   const int64_t row = q0 + n;
-  if (!active || row >= a.n_q) return;
+  if (row >= a.n_q) return;
 #pragma unroll
-  for (int h = 0; h < kH; ++h) {
-    const float l = o[h][1][0];  // valid in lane group 2 (e = 24)
+  for (int j = 0; j < kHw; ++j) {
+    const int h = kHw * wave + j;
+    const float l = o[j][1][0];  // valid in lane group 2 (e = 24)
     if (g == 2) {
       const bool empty = !(l > 0.0f);
-      a.m_parts[((int64_t)part * kH + h) * a.n_q + row] = empty ? -INFINITY : m[h] - kShift;
+      a.m_parts[((int64_t)part * kH + h) * a.n_q + row] = empty ? -INFINITY : m[j] - kShift;
       a.l_parts[((int64_t)part * kH + h) * a.n_q + row] = empty ? 0.0f : l;
     }
     float* accp = a.acc_parts + (((int64_t)part * a.n_q + row) * kH + h) * kD;
-    *reinterpret_cast<float4*>(accp + 4 * g) = make_float4(o[h][0][0], o[h][0][1], o[h][0][2], o[h][0][3]);
+    *reinterpret_cast<float4*>(accp + 4 * g) = make_float4(o[j][0][0], o[j][0][1], o[j][0][2], o[j][0][3]);
     if (g < 2)
-      *reinterpret_cast<float4*>(accp + 16 + 4 * g) = make_float4(o[h][1][0], o[h][1][1], o[h][1][2], o[h][1][3]);
+      *reinterpret_cast<float4*>(accp + 16 + 4 * g) = make_float4(o[j][1][0], o[j][1][1], o[j][1][2], o[j][1][3]);
   }
 }
 
@@ -589,17 +623,10 @@ __global__ void __launch_bounds__(64) bias_kernel(FastBiasArgs a) {
 }  // namespace
 
 hipError_t launch_fast_attn(const FastAttnArgs& a, hipStream_t st) {
-  const int64_t n_qt = a.nq_pad / kTileQ;
-  const int64_t n_rg = (n_qt + kWaves - 1) / kWaves;
-  const int64_t parts = (int64_t)a.n_kb * a.n_seg;
-  FastAttnArgs b = a;
-  // numbered per XCD only where every XCD then holds at least 32 row groups
-  // (a round of its CUs) of each part, which keeps the XCDs evenly loaded
-  b.xcd_order = n_rg >= 256 && parts > 1;
-  if (b.xcd_order)
-    hipLaunchKernelGGL(attn_kernel, dim3((unsigned)(8 * ((n_rg + 7) / 8) * parts)), dim3(64 * kWaves), 0, st, b);
-  else
-    hipLaunchKernelGGL(attn_kernel, dim3((unsigned)n_rg, (unsigned)parts), dim3(64 * kWaves), 0, st, b);
+  // row groups vary fastest: the resident workgroups stream the same keys, whose
+  // k and v the XCDs' L2 then serve
+  hipLaunchKernelGGL(attn_kernel, dim3((unsigned)(a.nq_pad / kTileQ), (unsigned)a.n_parts), dim3(64 * kWaves), 0, st,
+                     a);
   return hipGetLastError();
 }
 

@@ -220,3 +220,18 @@ def test_grid12000_stripes_sampled(torch_cuda):
         err = rel_err(got[np.array(rows) - q0], d.oracle_rows(rows))
         log(f"  stripe {q0}: {len(rows)} rows rel err {err:.3e}")
         assert err <= TOL_BF16
+
+
+@pytest.mark.parametrize("n_tok,q_row0,n_q,n_kb", [(1, 0, 1, 1), (16, 0, 16, 16), (47, 30, 17, 2), (130, 1, 1, 130),
+                                                   (1100, 1083, 17, 9), (1100, 500, 33, 1000), (2050, 7, 40, 64)])
+def test_part_partition_edges(torch_cuda, n_tok, q_row0, n_q, n_kb):
+    """Row tiles and key parts at their edges: one row, one key, parts of one 16-key tile, more key
+    blocks than tiles, a last tile of a few keys; against the oracle, and one block against many."""
+    log(f"case N={n_tok} rows {q_row0}+{n_q} n_kb={n_kb}")
+    m = np.ones(n_tok, np.uint8)
+    m[5:n_tok - 1:11] = 0
+    d = Device(workload(n_tok=n_tok), mask=m)
+    got = _np(d.attention(q_row0, n_q, n_kb))
+    assert rel_err(got, d.oracle_rows(np.arange(q_row0, q_row0 + n_q))) <= TOL_BF16
+    assert rel_err(_np(d.attention(q_row0, n_q, 1)), got) <= TOL_BLOCKED
+    assert np.array_equal(_np(d.attention(q_row0, n_q, n_kb)), got)
