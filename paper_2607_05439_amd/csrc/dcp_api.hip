@@ -105,7 +105,7 @@ int fast_segments(int64_t n_tok, int64_t n_q, int32_t n_kb) {
 // 512; what a part costs, in keys at the rate of a full round (0.31 us per key of
 // 512 workgroups, 6.75 TB/s), was fitted to sweeps of the part count on 200 to 24000
 // tokens: a full round its keys; a last, partial round r workgroups' share of
-// the stream, but at least 0.45 of a round's time per key alone on a CU and 0.87
+// the stream, but at least 0.45 of a round's time per key alone on a CU and 0.94
 // with two on some; each round 51 keys for its start and end; and each partial
 // state 0.0021 per row for writing and merging it. 1024 tokens: 54 us at 4 or 8
 // parts (256 or 512 workgroups), 65 at 16, 69 at 5; 4800 tokens: 922 us at 5, 1007
@@ -129,7 +129,7 @@ int fast_parts(int64_t k_lo, int64_t k_len, int64_t n_q, int64_t max_parts) {
     const int64_t full = groups * p / 512, r = groups * p % 512;
     double cost = (double)full * (keys + 51.0) + 0.0021 * (double)(n_q * p);
     if (r > 0) {
-      const double alone = r <= 256 ? 0.45 : 0.87, share = (double)r / 512.0;
+      const double alone = r <= 256 ? 0.45 : 0.94, share = (double)r / 512.0;
       cost += keys * (alone > share ? alone : share) + 51.0;
     }
     if (p == first || cost < best) {
@@ -241,6 +241,12 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
   hipError_t e;
   const int32_t log2_units = path == kPathFast ? 1 : 0;
   bool merged = false;  // the attention kernel already wrote the result
+  // The gate: into the workspace for the merge, straight to a caller who wants it
+  // with the partial state (copied there if the 16-byte stores do not fit), or
+  // not at all.
+  float* gate = reinterpret_cast<float*>(ws + L.off_g);
+  const bool gate_copy = part && part->gate && !aligned(part->gate, 16);
+  if (part && !gate_copy) gate = part->gate;
   if (path == kPathFast) {
     dcp::FastProjArgs pa{};
     pa.s = static_cast<const uint16_t*>(s);
@@ -254,11 +260,14 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.n_q = n_q;
     pa.nq_pad = L.nq_pad;
     pa.n_pad = L.n_pad;
+    // only the keys of the range, and the gate only where it goes somewhere
+    pa.key_tile0 = k_lo / dcp::kTileK;
+    pa.key_tiles = k_len > 0 ? (k_lo + k_len + dcp::kTileK - 1) / dcp::kTileK - pa.key_tile0 : 0;
     pa.c_s = shape->c_s;
     pa.q = reinterpret_cast<uint16_t*>(ws + L.off_q);
     pa.k = reinterpret_cast<uint16_t*>(ws + L.off_k);
     pa.vt = reinterpret_cast<uint16_t*>(ws + L.off_v);
-    pa.g = reinterpret_cast<float*>(ws + L.off_g);
+    pa.g = gate;
     pa.tile_valid = reinterpret_cast<uint32_t*>(ws + L.off_tv);
     pa.w_split = ws + L.off_ws;
     if ((e = dcp::launch_fast_proj(pa, st)) != hipSuccess)
@@ -308,7 +317,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.q = reinterpret_cast<float*>(ws + L.off_q);
     pa.k = reinterpret_cast<float*>(ws + L.off_k);
     pa.v = reinterpret_cast<float*>(ws + L.off_v);
-    pa.g = reinterpret_cast<float*>(ws + L.off_g);
+    pa.g = gate;
     if ((e = dcp::launch_gen_proj(pa, st)) != hipSuccess)
       return fail(DCP_ERR_HIP, "projection launch failed: %s", hipGetErrorString(e));
     dcp::GenAttnArgs aa{};
@@ -371,7 +380,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     ma.l_out = part->l;
     ma.acc_out = part->acc;
     ma.m_natural = 1;
-    if (part->gate && (e = hipMemcpyAsync(part->gate, ws + L.off_g, (size_t)n_q * hd * sizeof(float),
+    if (gate_copy && (e = hipMemcpyAsync(part->gate, ws + L.off_g, (size_t)n_q * hd * sizeof(float),
                                           hipMemcpyDeviceToDevice, st)) != hipSuccess)
       return fail(DCP_ERR_HIP, "gate copy failed: %s", hipGetErrorString(e));
   } else {

@@ -42,6 +42,7 @@ struct FastProjArgs {
   const float *w_q, *w_k, *w_v, *w_g;
   const uint8_t* mask;  // [N] or null
   int64_t n_tok, q_row0, n_q, nq_pad, n_pad;
+  int64_t key_tile0, key_tiles;  // k, vt and tile_valid are written for these 16-key tiles
   int32_t c_s;
   uint16_t* q;   // [H][nq_pad][32] bf16, scaled by log2(e)/sqrt(d)
   uint16_t* k;   // [H][n_pad][32] bf16
@@ -79,7 +80,7 @@ struct GenProjArgs {
   const float *w_q, *w_k, *w_v, *w_g;
   int64_t n_tok, q_row0, n_q;
   int32_t c_s, hd;
-  float *q, *k, *v, *g;  // q, g: [n_q][hd]; k, v: [N][hd]; g holds the sigmoid (16-byte aligned)
+  float *q, *k, *v, *g;  // q, g: [n_q][hd]; k, v: [N][hd]; g holds the sigmoid (16-byte aligned, or null: not wanted)
   const uint8_t* mask;   // [N] or null: v of masked keys is written as 0
   int32_t kv_head_dim;   // k, v in the tiled attention's layout, with this head size; 0: row-major [N][hd]
   int32_t s_vec;         // set by the launcher: rows of s take 4-element loads

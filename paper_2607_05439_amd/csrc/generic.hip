@@ -97,6 +97,7 @@ __global__ void __launch_bounds__(256) gen_proj_kernel(GenProjArgs a) {
   const int o0 = (second ? ot - n_ot : ot) * (16 * T);
   const float* w = q_side ? (second ? a.w_g : a.w_q) : (second ? a.w_v : a.w_k);
   float* dst = q_side ? (second ? a.g : a.q) : (second ? a.v : a.k);
+  if (!dst) return;
   const bool w_vec = a.s_vec && (reinterpret_cast<uintptr_t>(w) & 15) == 0;
   int64_t s_base[T], w_base[T];
 #pragma unroll

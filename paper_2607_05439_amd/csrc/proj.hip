@@ -10,7 +10,7 @@
 //   tile_valid [n_pad / 16]: bit i = key 16 t + i exists and attends
 // Matrix-core operand layouts as in fast.hip (v_mfma_f32_16x16x32_bf16).
 //
-// Two kernels:
+// Kernels:
 //   proj_split_kernel  the four weight matrices, split into bf16 hi + lo and
 //                      laid out as matrix-core operands: for projection p,
 //                      16-output tile j (rows 16 j .. 16 j + 15 of W_p, which
@@ -25,6 +25,7 @@
 //                      of one head and the start of the next); each wave
 //                      takes two tiles over 128 tokens (64 or 32 on small
 //                      layers, so that the launch still fills the chip).
+//   proj_small_kernel  both in one for the smallest layers.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -75,6 +76,177 @@ __global__ void __launch_bounds__(256) proj_split_kernel(FastProjArgs a) {
   *reinterpret_cast<bf16x4*>(dst + 1024) = lo;
 }
 
+// Writes one finished tile: acc = projection `which` of outputs 16 j + 4g .. +3
+// for token 16 tile + n (of the stripe for q and g).
+__device__ __forceinline__ void proj_store(const FastProjArgs& a, int which, int j, int64_t tile, int lane,
+                                           const f32x4& acc) {
+  const int n = lane & 15, g = lane >> 4;
+  const int64_t t0 = tile * 16;
+  if (which == 2) {
+    // transposed through the matrix cores: the accumulator's registers as
+    // an A operand of the k = 16 product hold the tile's transpose, and
+    // times the identity that lands in the accumulator layout (exact: the
+    // bf16 values times 1). Then vt[i] = v[token t0 + 4g + i][output
+    // 16 j + n]: for its head h and e = output % 24, the V^T operand item
+    // (lane 16 g + e % 16, M-tile e / 16) of keys 4g .. 4g + 3. Rows
+    // e >= 16 also write row e + 8: the ones row (e + 8 = 24) or a zero row.
+    bf16x4 av, id;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      av[i] = (__bf16)acc[i];
+      id[i] = (__bf16)(4 * g + i == n ? 1.0f : 0.0f);
+    }
+    const f32x4 vt = mfma16(av, id, f32x4{0.f, 0.f, 0.f, 0.f});
+    const int o = 16 * j + n, h = o / kD, e = o % kD;
+    bf16x4 val, pad;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t tok = t0 + 4 * g + i;
+      const bool valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
+      val[i] = (__bf16)(valid ? vt[i] : 0.0f);
+      pad[i] = (__bf16)(valid && e == 16 ? 1.0f : 0.0f);
+    }
+    u32x2* dst = reinterpret_cast<u32x2*>(a.vt) + (((int64_t)h * (a.n_pad / 16) + tile) * 64 + 16 * g) * 2;
+    dst[(e % 16) * 2 + e / 16] = __builtin_bit_cast(u32x2, val);
+    if (e >= 16) dst[(e - 8) * 2 + 1] = __builtin_bit_cast(u32x2, pad);
+    return;
+  }
+  // acc[i] = proj[output 16 j + 4g + i][token t0 + n]; the four
+  // outputs lie in one head (24 is a multiple of 4)
+  const int64_t tok = t0 + n;
+  const int o = 16 * j + 4 * g, h = o / kD, e = o % kD;
+  if (which == 3) {
+    if (tok >= a.n_q) return;
+    f32x4 sg;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sg[i] = 1.0f / (1.0f + __expf(-acc[i]));
+    *reinterpret_cast<f32x4*>(a.g + tok * kHD + o) = sg;
+    return;
+  }
+  if (which == 1 && j == 0) {
+    // per-tile key mask: bit i = token t0 + i exists and attends
+    const bool kv_valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
+    const uint32_t bits = (uint32_t)(__ballot(kv_valid) & 0xFFFFull);
+    if (lane == 0) a.tile_valid[tile] = bits;
+  }
+  bool valid;
+  float scale;
+  uint16_t* dst;
+  if (which == 0) {
+    valid = tok < a.n_q;
+    scale = kLog2e * 0.20412414523193150818f;  // log2(e) / sqrt(24)
+    dst = a.q + ((int64_t)h * a.nq_pad + tok) * kDp;
+  } else {
+    valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
+    scale = 1.0f;
+    dst = a.k + ((int64_t)h * a.n_pad + tok) * kDp;
+  }
+  bf16x4 val;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) val[i] = (__bf16)(valid ? acc[i] * scale : 0.0f);
+  *reinterpret_cast<u32x2*>(dst + e) = __builtin_bit_cast(u32x2, val);
+  if (e == kD - 4) *reinterpret_cast<u32x4*>(dst + kD) = u32x4{0u, 0u, 0u, 0u};  // e = 24 .. 31
+}
+
+// The projections of a small layer in one kernel, without prepared weights: a
+// wave takes one output tile and two token tiles. Its 16 fp32 weight rows and the
+// workgroup's 32 rows of s, 384 channels at a time, are copied into LDS all at
+// once (consecutive kilobytes; 16-byte chunks XOR-swizzled by row, so an operand's
+// 16 rows cover all banks), and the weights are split into hi + lo on their way to
+// the registers: proj_kernel's operands and sums, bit for bit. One trip to
+// memory instead of a chain of a dozen k-steps after a launch of its own.
+constexpr int kSmallTiles = 2, kSmallSteps = 12, kSmallWaves = 2;
+constexpr int64_t kSmallMaxTiles = 80;
+constexpr int kSmallSChunks = kSmallSteps * 4;  // 16-byte chunks of a staged row of s
+constexpr int kSmallWChunks = kSmallSteps * 8;  // of a weight row
+__global__ void __launch_bounds__(64 * kSmallWaves) proj_small_kernel(FastProjArgs a) {
+  __shared__ __attribute__((aligned(16))) u32x4 s_s[kSmallTiles * 16 * kSmallSChunks];       // 24 KB
+  __shared__ __attribute__((aligned(16))) u32x4 s_w[kSmallWaves][16 * kSmallWChunks];        // 24 KB each
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the hardware deals workgroup i to XCD i % 8: each XCD reads an eighth of the
+  // weights (columns of kSmallWaves output tiles, first the key side's)
+  constexpr int kSideCols = 2 * kOutTiles / kSmallWaves, kXcdCols = 2 * kSideCols / 8;
+  const int col = (int)(blockIdx.x & 7) * kXcdCols + (int)(blockIdx.x >> 3) % kXcdCols;
+  const int64_t group = (blockIdx.x >> 3) / kXcdCols;
+  const bool is_query = col >= kSideCols;
+  const int out = (is_query ? col - kSideCols : col) * kSmallWaves + wave;  // 0..47: the side's two projections
+  const bool second = out >= kOutTiles;                                     // the same for the whole workgroup
+  const int which = is_query ? (second ? 3 : 0) : (second ? 2 : 1);
+  const int j = second ? out - kOutTiles : out;
+  const int64_t tile0 = (is_query ? 0 : a.key_tile0) + group * kSmallTiles;
+  const int64_t tile_end = is_query ? a.nq_pad / 16 : a.key_tile0 + a.key_tiles;
+  if (tile0 >= tile_end || (which == 3 && !a.g)) return;  // the whole workgroup, before any barrier
+  const int64_t n_valid = is_query ? a.n_q : a.n_tok;
+  const int64_t base_tok = is_query ? a.q_row0 : 0;
+  const float* w = which == 0 ? a.w_q : which == 1 ? a.w_k : which == 2 ? a.w_v : a.w_g;
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(w) + (int64_t)16 * j * a.c_s, 0, 16 * a.c_s * 4, kRawBufferFlags);
+  const int last_row = (int)min(n_valid - tile0 * 16, (int64_t)(16 * kSmallTiles)) - 1;  // rows past it repeat it
+  const __amdgpu_buffer_rsrc_t sres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(a.s + (base_tok + tile0 * 16) * a.c_s), 0, (last_row + 1) * a.c_s * 2, kRawBufferFlags);
+  f32x4 acc[kSmallTiles];
+#pragma unroll
+  for (int u = 0; u < kSmallTiles; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < a.c_s; c0 += 32 * kSmallSteps) {
+    if (c0 > 0) __syncthreads();  // every wave is done with what was staged before
+    // Three loads cover two weight rows (four rows of s); a row's bits of the
+    // swizzle split into the lane's part and the loop's, so an address is two
+    // instructions. Channels past c_s read out of range: zeros.
+    const bool whole = c0 + 32 * kSmallSteps <= a.c_s;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int row = (64 * r + lane) / kSmallWChunks, sw = ((64 * r + lane) % kSmallWChunks) ^ row;
+      const int at = (row * a.c_s + c0) * 4;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int ch = sw ^ (2 * m);
+        int off = at + 16 * ch;
+        if (!whole) off = c0 + 4 * ch < a.c_s ? off : kOutOfRange;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(wres, (__attribute__((address_space(3))) void*)&s_w[wave][64 * (3 * m + r)],
+                                                 16, off, 2 * m * a.c_s * 4, 0, 0);
+      }
+    }
+    static_assert(kSmallWaves == 2 && kSmallTiles == 2, "16 rows of s per wave");
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int row = (64 * r + lane) / kSmallSChunks, sw = ((64 * r + lane) % kSmallSChunks) ^ row;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int ch = sw ^ (4 * m);
+        int off = (min(16 * wave + 4 * m + row, last_row) * a.c_s + c0 + 8 * ch) * 2;
+        if (!whole) off = c0 + 8 * ch < a.c_s ? off : kOutOfRange;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            sres, (__attribute__((address_space(3))) void*)&s_s[16 * kSmallSChunks * wave + 64 * (3 * m + r)], 16, off, 0,
+            0, 0);
+      }
+    }
+    __syncthreads();  // waits for the copies
+#pragma unroll 4
+    for (int ks = 0; ks < kSmallSteps; ++ks) {
+      const u32x4 w0 = s_w[wave][n * kSmallWChunks + ((8 * ks + 2 * g) ^ n)];
+      const u32x4 w1 = s_w[wave][n * kSmallWChunks + ((8 * ks + 2 * g + 1) ^ n)];
+      bf16x8 hi, lo;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float x = __uint_as_float(i < 4 ? w0[i & 3] : w1[i & 3]);
+        const __bf16 hv = (__bf16)x;
+        hi[i] = hv;
+        lo[i] = (__bf16)(x - (float)hv);
+      }
+#pragma unroll
+      for (int u = 0; u < kSmallTiles; ++u) {
+        const bf16x8 sv = as_bf16x8(s_s[(16 * u + n) * kSmallSChunks + ((4 * ks + g) ^ n)]);
+        acc[u] = mfma32(hi, sv, acc[u]);
+        acc[u] = mfma32(lo, sv, acc[u]);
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kSmallTiles; ++u)
+    if (tile0 + u < tile_end) proj_store(a, which, j, tile0 + u, lane, acc[u]);
+}
+
 // One workgroup = TILES x 16 tokens (128 when TILES = 8; fewer tiles per
 // workgroup, and so more workgroups, when the token count is small) x one side (query: q and g of the stripe's rows;
 // key: k and v of all tokens) x 16 of the side's 48 output tiles; wave w of
@@ -100,7 +272,7 @@ __global__ void __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_p
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int64_t item = (int64_t)(slot / kProjSideWgs) * 8 + xcd;  // key groups first, then query groups
   const int pair = (slot % kProjSideWgs) * kProjWaves + wave;     // 0..23 within the side
-  const int64_t key_groups = (a.n_pad / 16 + kProjTiles - 1) / kProjTiles;
+  const int64_t key_groups = (a.key_tiles + kProjTiles - 1) / kProjTiles;
   const int64_t query_groups = (a.nq_pad / 16 + kProjTiles - 1) / kProjTiles;
   if (item >= key_groups + query_groups) return;  // the whole workgroup, before any barrier
   const bool is_query = item >= key_groups;
@@ -108,10 +280,10 @@ __global__ void __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_p
   const bool second = pair >= kOutTiles / 2;                          // g or v
   const int which = is_query ? (second ? 3 : 0) : (second ? 2 : 1);  // 0 q, 1 k, 2 v, 3 g
   const int j0 = 2 * (pair % (kOutTiles / 2));                        // first of the wave's two output tiles
-  const int64_t limit = is_query ? a.nq_pad : a.n_pad;
+  const int64_t tile_end = is_query ? a.nq_pad / 16 : a.key_tile0 + a.key_tiles;
   const int64_t n_valid = is_query ? a.n_q : a.n_tok;
   const int64_t base_tok = is_query ? a.q_row0 : 0;
-  const int64_t tile0 = grp * kProjTiles;
+  const int64_t tile0 = grp * kProjTiles + (is_query ? 0 : a.key_tile0);
 
   // Staging goes straight to LDS (16 bytes per lane): the workgroup's 2 TILES KB
   // per chunk are 2 TILES blocks of 8 rows, block b copied by wave b % 8; lane i of
@@ -188,76 +360,9 @@ __global__ void __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_p
 #pragma unroll
   for (int u = 0; u < kProjTiles; ++u) {
     const int64_t tile = tile0 + u;
-    if (tile * 16 >= limit) break;
-    const int64_t t0 = tile * 16;
-#pragma unroll
-    for (int jt = 0; jt < 2; ++jt) {
-      const int j = j0 + jt;
-      if (which == 2) {
-        // transposed through the matrix cores: the accumulator's registers as
-        // an A operand of the k = 16 product hold the tile's transpose, and
-        // times the identity that lands in the accumulator layout (exact: the
-        // bf16 values times 1). Then vt[i] = v[token t0 + 4g + i][output
-        // 16 j + n]: for its head h and e = output % 24, the V^T operand item
-        // (lane 16 g + e % 16, M-tile e / 16) of keys 4g .. 4g + 3. Rows
-        // e >= 16 also write row e + 8: the ones row (e + 8 = 24) or a zero row.
-        bf16x4 av, id;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          av[i] = (__bf16)acc[u][jt][i];
-          id[i] = (__bf16)(4 * g + i == n ? 1.0f : 0.0f);
-        }
-        const f32x4 vt = mfma16(av, id, f32x4{0.f, 0.f, 0.f, 0.f});
-        const int o = 16 * j + n, h = o / kD, e = o % kD;
-        bf16x4 val, pad;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t tok = t0 + 4 * g + i;
-          const bool valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
-          val[i] = (__bf16)(valid ? vt[i] : 0.0f);
-          pad[i] = (__bf16)(valid && e == 16 ? 1.0f : 0.0f);
-        }
-        u32x2* dst = reinterpret_cast<u32x2*>(a.vt) + (((int64_t)h * (a.n_pad / 16) + tile) * 64 + 16 * g) * 2;
-        dst[(e % 16) * 2 + e / 16] = __builtin_bit_cast(u32x2, val);
-        if (e >= 16) dst[(e - 8) * 2 + 1] = __builtin_bit_cast(u32x2, pad);
-        continue;
-      }
-      // acc[u][jt][i] = proj[output 16 j + 4g + i][token t0 + n]; the four
-      // outputs lie in one head (24 is a multiple of 4)
-      const int64_t tok = t0 + n;
-      const int o = 16 * j + 4 * g, h = o / kD, e = o % kD;
-      if (which == 3) {
-        if (tok >= a.n_q) continue;
-        f32x4 sg;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sg[i] = 1.0f / (1.0f + __expf(-acc[u][jt][i]));
-        *reinterpret_cast<f32x4*>(a.g + tok * kHD + o) = sg;
-        continue;
-      }
-      if (which == 1 && j == 0) {
-        // per-tile key mask: bit i = token t0 + i exists and attends
-        const bool kv_valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
-        const uint32_t bits = (uint32_t)(__ballot(kv_valid) & 0xFFFFull);
-        if (lane == 0) a.tile_valid[tile] = bits;
-      }
-      bool valid;
-      float scale;
-      uint16_t* dst;
-      if (which == 0) {
-        valid = tok < a.n_q;
-        scale = kLog2e * 0.20412414523193150818f;  // log2(e) / sqrt(24)
-        dst = a.q + ((int64_t)h * a.nq_pad + tok) * kDp;
-      } else {
-        valid = tok < a.n_tok && (a.mask == nullptr || a.mask[tok] != 0);
-        scale = 1.0f;
-        dst = a.k + ((int64_t)h * a.n_pad + tok) * kDp;
-      }
-      bf16x4 val;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) val[i] = (__bf16)(valid ? acc[u][jt][i] * scale : 0.0f);
-      *reinterpret_cast<u32x2*>(dst + e) = __builtin_bit_cast(u32x2, val);
-      if (e == kD - 4) *reinterpret_cast<u32x4*>(dst + kD) = u32x4{0u, 0u, 0u, 0u};  // e = 24 .. 31
-    }
+    if (tile >= tile_end || (which == 3 && !a.g)) break;
+    proj_store(a, which, j0, tile, lane, acc[u][0]);
+    proj_store(a, which, j0 + 1, tile, lane, acc[u][1]);
   }
 }
 
@@ -266,6 +371,17 @@ __global__ void __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_p
 size_t fast_proj_split_bytes(int32_t c_s) { return (size_t)4 * kOutTiles * (c_s / 32) * 2048; }
 
 hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st) {
+  // One kernel up to 80 token tiles of 16 (both sides together), where the chain of
+  // proj_kernel's k-steps and the split's launch weigh more than splitting the
+  // weights again for every two tiles: a whole layer of 60 tokens 31.9 -> 22.4 us,
+  // 333 38.4 -> 32.7, 500 40.9 -> 38.3; 700 (88 tiles) 48.9 -> 49.9, 1024 70.3 -> 72.6.
+  if (a.key_tiles + a.nq_pad / 16 <= kSmallMaxTiles) {
+    const int64_t tiles = max(a.key_tiles, a.nq_pad / 16);
+    const int64_t groups = (tiles + kSmallTiles - 1) / kSmallTiles;
+    hipLaunchKernelGGL(proj_small_kernel, dim3((unsigned)(groups * 4 * kOutTiles / kSmallWaves)), dim3(64 * kSmallWaves),
+                       0, st, a);
+    return hipGetLastError();
+  }
   const int64_t split_threads = (int64_t)4 * kHD * (a.c_s / 4);
   hipLaunchKernelGGL(proj_split_kernel, dim3((unsigned)((split_threads + 255) / 256)), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
@@ -276,7 +392,7 @@ hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st) {
   // 0.106 -> 0.093 ms, a 4800-token one -0.8%; each wave's weights are then
   // applied to fewer tokens, which costs more than it saves on larger layers).
   auto workgroups = [&](int tiles) {
-    const int64_t items = (a.n_pad / 16 + tiles - 1) / tiles + (a.nq_pad / 16 + tiles - 1) / tiles;
+    const int64_t items = (a.key_tiles + tiles - 1) / tiles + (a.nq_pad / 16 + tiles - 1) / tiles;
     return (items + 7) / 8 * 8 * kProjSideWgs;
   };
   const int64_t w8 = workgroups(8), w4 = workgroups(4), w2 = workgroups(2);

@@ -90,3 +90,38 @@ def test_empty_and_fully_masked_ranges_give_the_empty_state():
         log(f"case empty range [{k0}, {k1})")
         assert np.all(np.isneginf(m)) and np.all(l == 0.0) and np.all(acc == 0.0)
         assert np.all(np.isfinite(g)) and np.all((g > 0) & (g < 1))
+
+
+@pytest.mark.parametrize("c_s", [32, 352, 384, 416, 800])
+def test_small_and_large_projections_agree(c_s):
+    """The one-kernel projection of small calls against the two-kernel one of large calls: rows of
+    a 1300-token layer as a stripe over a short key range (few tiles) and inside a call over many
+    rows; the operands are the same bits, so only the attention's fp32 order may differ. A gate
+    that is not asked for, and one off 16-byte alignment."""
+    import torch
+    d = Device(workload(n_tok=1300, c_s=c_s, mask="random:40"))
+    few = partial(d, 700, 33, 650, 1000)
+    many = partial(d, 100, 1200, 650, 1000)
+    for a, b in zip(few[:3], (many[0][:, 600:633], many[1][:, 600:633], many[2][600:633])):
+        assert rel_err(torch.nan_to_num(a, neginf=0.0).cpu().numpy(), torch.nan_to_num(b, neginf=0.0).cpu().numpy()) <= 1e-6
+    assert torch.equal(few[3], many[3][600:633])
+
+
+@pytest.mark.parametrize("name,n_q,k0,k1", [("tiny128_f32", 40, 3, 90), ("pad1024_bf16", 40, 100, 300),
+                                            ("pad1024_bf16", 1000, 0, 1024)])
+def test_gate_not_wanted_or_unaligned(name, n_q, k0, k1):
+    """A NULL gate_out, and one off the 16-byte alignment of the direct stores: the same state and gate."""
+    import torch
+    import paper_2607_05439_amd as dcp
+    d = Device(workload(name))
+    want = partial(d, 8, n_q, k0, k1)
+    shape = d.shape(DCP_F32)
+    ws = torch.empty(dcp.dcp_workspace_size(shape, n_q, 1), dtype=torch.uint8, device=d.dev)
+    z_ptr = d.z.data_ptr() + 8 * d.wl.n_tok * d.wl.c_z * d.z.element_size()
+    off = torch.full((want[3].numel() + 1,), 7.0, device=d.dev)
+    for gate in (None, off[1:]):
+        m, l, acc = (torch.full_like(t, 7.0) for t in want[:3])
+        dcp.dcp_pair_bias_attention_partial(shape, d.weights(), d.s, z_ptr, d.mask, 8, n_q, k0, k1, m, l, acc, gate,
+                                            ws, ws.numel(), None)
+        assert all(torch.equal(a, b) for a, b in zip((m, l, acc), want[:3]))
+    assert torch.equal(off[1:].view_as(want[3]), want[3]) and off[0].item() == 7.0
