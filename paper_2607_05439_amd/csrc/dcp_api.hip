@@ -227,7 +227,26 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     return fail(DCP_ERR_INVALID_ARGUMENT, "w_q, w_k, w_v, w_g, w_b and ln_gamma must be 16-byte aligned");
   Layout L;
   make_layout(shape, path, n_q, n_key_blocks, &L);
-  if (path == kPathFast && k_len > 0) L.n_parts = fast_parts(k_lo, k_len, n_q, L.n_parts);
+  const int64_t key_tile0 = k_lo / dcp::kTileK;
+  const int64_t key_tiles = k_len > 0 ? (k_lo + k_len + dcp::kTileK - 1) / dcp::kTileK - key_tile0 : 0;
+  const bool small = path == kPathFast && dcp::fast_proj_small(key_tiles, L.nq_pad / dcp::kTileQ);
+  if (path == kPathFast && k_len > 0) {
+    if (small) {
+      // no split weights: their room goes to the gate and to more parts, which a
+      // few query rows need to reach the whole chip (60 tokens 22.2 us in one part,
+      // 17.3 in four; 333 tokens 32.4 in the five of the layout, 29.6 in seven)
+      const size_t hd = (size_t)shape->n_heads * shape->head_dim, stats = (size_t)shape->n_heads * n_q * 4;
+      L.off_g = L.off_ws;
+      const size_t off = L.off_g + round_up((size_t)n_q * hd * 4, 256), acc = (size_t)n_q * hd * 4;
+      const int64_t fit = (int64_t)((L.total - off - 2 * 256) / (2 * stats + acc));
+      L.n_parts = fast_parts(k_lo, k_len, n_q, fit);
+      L.off_m = off;
+      L.off_l = L.off_m + round_up(L.n_parts * stats, 256);
+      L.off_acc = L.off_l + round_up(L.n_parts * stats, 256);
+    } else {
+      L.n_parts = fast_parts(k_lo, k_len, n_q, L.n_parts);
+    }
+  }
   if (!workspace || !aligned(workspace, 256))
     return fail(DCP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
   if (workspace_bytes < L.total)
@@ -261,8 +280,8 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.nq_pad = L.nq_pad;
     pa.n_pad = L.n_pad;
     // only the keys of the range, and the gate only where it goes somewhere
-    pa.key_tile0 = k_lo / dcp::kTileK;
-    pa.key_tiles = k_len > 0 ? (k_lo + k_len + dcp::kTileK - 1) / dcp::kTileK - pa.key_tile0 : 0;
+    pa.key_tile0 = key_tile0;
+    pa.key_tiles = key_tiles;
     pa.c_s = shape->c_s;
     pa.q = reinterpret_cast<uint16_t*>(ws + L.off_q);
     pa.k = reinterpret_cast<uint16_t*>(ws + L.off_k);

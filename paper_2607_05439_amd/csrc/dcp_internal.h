@@ -223,6 +223,7 @@ struct ScatterArgs {
 };
 
 size_t fast_proj_split_bytes(int32_t c_s);
+bool fast_proj_small(int64_t key_tiles, int64_t query_tiles);  // one kernel, w_split unused
 hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st);
 hipError_t launch_fast_attn(const FastAttnArgs& a, hipStream_t st);
 hipError_t launch_fast_bias(const FastBiasArgs& a, hipStream_t st);

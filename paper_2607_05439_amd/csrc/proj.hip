@@ -370,12 +370,14 @@ __global__ void __launch_bounds__(64 * kProjWaves) __attribute__((amdgpu_waves_p
 
 size_t fast_proj_split_bytes(int32_t c_s) { return (size_t)4 * kOutTiles * (c_s / 32) * 2048; }
 
+// One kernel up to 80 token tiles of 16 (both sides together), where the chain of
+// proj_kernel's k-steps and the split's launch weigh more than splitting the
+// weights again for every two tiles: a whole layer of 60 tokens 31.9 -> 22.4 us,
+// 333 38.4 -> 32.7, 500 40.9 -> 38.3; 700 (88 tiles) 48.9 -> 49.9, 1024 70.3 -> 72.6.
+bool fast_proj_small(int64_t key_tiles, int64_t query_tiles) { return key_tiles + query_tiles <= kSmallMaxTiles; }
+
 hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st) {
-  // One kernel up to 80 token tiles of 16 (both sides together), where the chain of
-  // proj_kernel's k-steps and the split's launch weigh more than splitting the
-  // weights again for every two tiles: a whole layer of 60 tokens 31.9 -> 22.4 us,
-  // 333 38.4 -> 32.7, 500 40.9 -> 38.3; 700 (88 tiles) 48.9 -> 49.9, 1024 70.3 -> 72.6.
-  if (a.key_tiles + a.nq_pad / 16 <= kSmallMaxTiles) {
+  if (fast_proj_small(a.key_tiles, a.nq_pad / 16)) {
     const int64_t tiles = max(a.key_tiles, a.nq_pad / 16);
     const int64_t groups = (tiles + kSmallTiles - 1) / kSmallTiles;
     hipLaunchKernelGGL(proj_small_kernel, dim3((unsigned)(groups * 4 * kOutTiles / kSmallWaves)), dim3(64 * kSmallWaves),
