@@ -12,29 +12,31 @@
 // entry (x, y, z, then |c|^2, or the group in the group modes) and, for every
 // step of 128 consecutive candidates, its bounding box (low and high corner),
 // into the caller's workspace.
-// knn_kernel: a workgroup of 8 independent waves serves 32 consecutive query
-// rows, 4 per wave (their coordinates and thresholds are wave-uniform
-// scalars). A wave visits the candidates in groups of 16 steps (2048
-// candidates), starting at the group that holds the queries themselves when
+// knn_kernel: a workgroup of 8 independent waves serves 8 or 16 consecutive
+// query rows, one or two per wave (their coordinates and thresholds are
+// wave-uniform scalars). A wave visits the candidates in groups of 64 (32)
+// steps, starting at the group that holds the queries themselves when
 // they are candidates (their sequence neighbours are close in space, which
 // makes the thresholds tight early; the result does not depend on the order).
-// Per group it tests the 16 boxes against its 4 queries (the next group's
-// boxes are loaded meanwhile) and skips a step whose box distance (computed in
-// the definition's rounded operations, which bound every member's distance
-// from below) exceeds the current k-th distance of all 4 queries: an exact
+// Per group it tests the boxes against its queries, one pair per lane (the next
+// group's boxes are loaded meanwhile), and skips a step whose box distance
+// (computed in the definition's rounded operations, which bound every member's
+// distance from below) exceeds the current k-th distance of every query: an exact
 // exclusion, not a heuristic. Only the candidates of the remaining steps are
 // read, straight from the workspace (L2-resident): a lane takes two per step
-// and tests them against the 4 queries with a cheap conservative bound (|c|^2
+// and tests them against the queries with a cheap conservative bound (|c|^2
 // - 2 c.q by three multiply-adds against a per-query limit derived from the
 // current k-th distance with a proven rounding margin): no candidate that
 // could enter is rejected. Only where some lane passes does the step compute
-// the distances of the definition; the exact 64-bit key test then picks the
-// candidates that enter the query's 64-entry LDS buffer. The sorted top-k
-// lives in registers (entry 64s + lane in slot s); a full buffer is sorted
-// (bitonic network across lanes) and merged slot by slot: the lane-wise
-// minimum of a sorted slot and the reversed sorted carry is a bitonic sequence
-// that holds the 64 smallest of the two, the maximum holds the other 64, and
-// one bitonic merge pass sorts each.
+// the distances of the definition; the exact key test then picks the
+// candidates that enter the query's 64-entry LDS buffer. The top-k lives
+// unsorted in registers; a full buffer is taken in by selecting the k smallest
+// of both (a bisection on the k-th distance that counts keys by ballots), and
+// the lists are sorted once, at the end (bitonic network across lanes).
+// What bounds it: the selections' chains of compare, count and branch, and the
+// visits' loads, at 5 to 8 waves per SIMD. 24000 queries of 96000 candidates, k =
+// 128: 171 us, 238 when every full buffer was sorted and merged and four queries
+// shared a wave; 1000 of 1000: 22 us, 84.
 // topk_merge_kernel: one wave per row, a rank merge of two sorted lists.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -45,8 +47,6 @@ namespace dcp {
 namespace {
 
 constexpr int kKnnWaves = 8;
-constexpr int kKnnQ = 4;                          // query rows per wave
-constexpr int kKnnRows = kKnnWaves * kKnnQ;       // query rows per workgroup
 constexpr uint64_t kNoKey = ~0ULL;
 
 // Value of lane (lane ^ M).
@@ -106,10 +106,9 @@ __device__ __forceinline__ void wave_lds_sync() {
   asm volatile("" ::: "memory");
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-  return ((uint64_t)hi << 32) | lo;
+// Set bits of m below this lane's.
+__device__ __forceinline__ int mbcnt64(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // a wave-uniform value, held in a scalar register
@@ -117,19 +116,23 @@ __device__ __forceinline__ float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// State of one query row: its sorted top-k (KS slots of 64 keys), the number
-// of valid entries, the k-th key, and the LDS buffer of pending keys.
+// State of one query row: its top-k (KS slots of 64 keys, unsorted until the
+// end), the number of valid entries, a key that every later entry is below, and
+// the LDS buffer of pending keys.
 template <int KS>
 struct QueryTopk {
   uint64_t top[KS];
-  uint64_t tau;  // keys below tau may enter (kNoKey until k entries exist)
+  uint64_t tau;  // keys below tau may enter: the k-th distance and any index (kNoKey until k entries exist)
   int count, bcount;
   uint64_t* buf;
-  float x, y, z;
   int32_t g;
-  float mx, my, mz;  // -2 x, -2 y, -2 z (exact)
+  float mx, my, mz;  // -2 x, -2 y, -2 z (exact, as is halving them back)
   float qq, qn;      // |q|^2 and |q|
   float lim;         // prefilter bound on |c|^2 - 2 c.q for candidates that may still enter
+
+  __device__ __forceinline__ float x() const { return -0.5f * mx; }
+  __device__ __forceinline__ float y() const { return -0.5f * my; }
+  __device__ __forceinline__ float z() const { return -0.5f * mz; }
 
   // The prefilter computes e = |c|^2 - 2 c.q with three multiply-adds; the
   // exact distance is |c - q|^2 = e + |q|^2 up to rounding. If the rounded
@@ -157,27 +160,124 @@ struct QueryTopk {
     buf = b;
   }
 
-  // merge the bcount pending keys into the sorted top-k
+  // Take the bcount pending keys into the top-k: find a bound B with exactly k of
+  // the top and pending keys below it (all of them while there are at most k),
+  // and put the pending keys below B into slots whose keys are not. The slots
+  // stay unsorted until finish(). Counting the keys below a candidate bound is
+  // one comparison and one scalar population count per register, so a bit of
+  // the bound costs a few scalar instructions where a sort-and-merge costs a
+  // chain of cross-lane exchanges (27 stages per 64 keys).
   __device__ __forceinline__ void flush(int lane, int k) {
-    uint64_t carry = lane < bcount ? buf[lane] : kNoKey;
-    carry = wave_sort(carry, lane);
+    const uint64_t pend = lane < bcount ? buf[lane] : kNoKey;
+    wave_lds_sync();  // the buffer has been read before it is reused below
+    uint64_t bound = kNoKey;
+    if (count + bcount > k) {
+      const uint32_t ph = (uint32_t)(pend >> 32);
+      auto below = [&](uint32_t x) {  // keys with a distance below x
+        int c = __popcll(__ballot(ph < x));
+#pragma unroll
+        for (int s = 0; s < KS; ++s) c += __popcll(__ballot((uint32_t)(top[s] >> 32) < x));
+        return c;
+      };
+      // at most k distances lie below lo, more than k below up: step down from the
+      // largest distance held by halves of it (factors of 2), then bisect,
+      // ending as soon as a bound with exactly k below it turns up
+      uint32_t up = count == k ? (uint32_t)(tau >> 32) + 1 : 0xFFFFFFFFu, lo = 0;
+      int c_lo = 0;
+      if (count == k)
+        while (up > 0x00800000u) {
+          const int c = below(up - 0x00800000u);
+          if (c <= k) {
+            lo = up - 0x00800000u;
+            c_lo = c;
+            break;
+          }
+          up -= 0x00800000u;
+        }
+      while (c_lo != k && up - lo > 1) {
+        const uint32_t mid = lo + (up - lo) / 2;
+        const int c = below(mid);
+        if (c <= k) {
+          lo = mid;
+          c_lo = c;
+        } else {
+          up = mid;
+        }
+      }
+      bound = (uint64_t)lo << 32;
+      if (c_lo != k) {
+        // the k-th distance is lo and several keys share it: the bound lies among
+        // their indices (keys are unique, so some bound has exactly k below it)
+        for (int bit = 31; bit >= 0; --bit) {
+          const uint64_t cand = bound | (1u << bit);
+          int c = __popcll(__ballot(pend < cand));
+#pragma unroll
+          for (int s = 0; s < KS; ++s) c += __popcll(__ballot(top[s] < cand));
+          if (c <= k) bound = cand;
+        }
+      }
+    }
+    // pending keys below the bound, in order, into the slots to be replaced
+    const uint64_t in = __ballot(pend < bound);
+    const int n_in = __popcll(in);
+    if (pend < bound) buf[mbcnt64(in)] = pend;
+    wave_lds_sync();
+    int base = 0;
+    uint32_t far = 0;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const uint64_t r = xor_lane64<63>(carry);  // reversed: descending
-      const uint64_t lo = r < top[s] ? r : top[s];
-      const uint64_t hi = r < top[s] ? top[s] : r;
-      top[s] = bitonic_pass<64>(lo, lane);
-      if (s + 1 < KS) carry = bitonic_pass<64>(hi, lane);
+      const bool out = !(top[s] < bound);
+      const uint64_t m = __ballot(out);
+      const int r = base + mbcnt64(m);
+      if (out) top[s] = r < n_in ? buf[r] : kNoKey;
+      base += __popcll(m);
+      far = top[s] == kNoKey ? far : max(far, (uint32_t)(top[s] >> 32));
     }
     count = min(k, count + bcount);
     bcount = 0;
-    uint64_t last = top[0];  // slot of entry k - 1, chosen without dynamic register indexing
+    // keys above the largest distance held cannot enter
+    tau = kNoKey;
+    if (count == k) {
 #pragma unroll
-    for (int s = 1; s < KS; ++s)
-      if (s == ((k - 1) >> 6)) last = top[s];
-    tau = count == k ? readlane64(last, (k - 1) & 63) : kNoKey;
+      for (int m = 1; m < 64; m <<= 1) far = max(far, (uint32_t)__shfl_xor((int)far, m));
+      tau = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)far) << 32) | 0xFFFFFFFFu;
+    }
     set_limit();
     wave_lds_sync();  // the buffer has been read before it is refilled
+  }
+
+  // The slots in ascending order.
+  __device__ __forceinline__ void finish(int lane) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) top[s] = wave_sort(top[s], lane);
+    // runs of W slots pairwise into runs of 2 W: the minima and maxima of one
+    // and the reverse of the other are bitonic, and halve down to single slots
+#pragma unroll
+    for (int w = 1; w < KS; w <<= 1) {
+#pragma unroll
+      for (int s0 = 0; s0 < KS; s0 += 2 * w) {
+        uint64_t rev[KS];
+#pragma unroll
+        for (int i = 0; i < w; ++i) rev[i] = xor_lane64<63>(top[s0 + 2 * w - 1 - i]);
+#pragma unroll
+        for (int i = 0; i < w; ++i) {
+          const uint64_t x = top[s0 + i], y = rev[i];
+          top[s0 + i] = x < y ? x : y;
+          top[s0 + w + i] = x < y ? y : x;
+        }
+      }
+#pragma unroll
+      for (int h = w / 2; h >= 1; h >>= 1)
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+          if ((s & h) == 0) {
+            const uint64_t x = top[s], y = top[s + h];
+            top[s] = x < y ? x : y;
+            top[s + h] = x < y ? y : x;
+          }
+#pragma unroll
+      for (int s = 0; s < KS; ++s) top[s] = bitonic_pass<64>(top[s], lane);
+    }
   }
 
   // the exact test and the append of one 64-candidate step
@@ -192,8 +292,7 @@ struct QueryTopk {
     if (mask == 0) return;
     const int n_new = __popcll(mask);
     if (bcount + n_new > 64) flush(lane, k);
-    const int pos = bcount + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const int pos = bcount + mbcnt64(mask);
     if (take) buf[pos] = key;
     wave_lds_sync();
     bcount += n_new;
@@ -211,7 +310,6 @@ __device__ __forceinline__ float dist2(float qx, float qy, float qz, float4 c) {
 }
 
 constexpr int kStep = 128;   // candidates per bounding box
-constexpr int kGroup = 2048;  // candidates per group of 16 steps (one skip test per lane)
 constexpr int kSeedWords = 64;  // steps whose seed bit a wave keeps: 64 x 64
 
 // one wave per step of 128 candidates, two per lane
@@ -249,8 +347,11 @@ __global__ void __launch_bounds__(256) knn_prep_kernel(KnnArgs a) {
   }
 }
 
-template <int KS, int MODE>
+template <int KS, int MODE, int kKnnQ>
 __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 6 : 1))) knn_kernel(KnnArgs a) {
+  constexpr int kKnnRows = kKnnWaves * kKnnQ;  // query rows per workgroup
+  constexpr int kSteps = 64 / kKnnQ;           // steps per group: one box and query per lane
+  constexpr int64_t kGroup = kSteps * kStep;   // candidates per group
   __shared__ uint64_t s_buf[kKnnWaves][kKnnQ][64];
   __shared__ uint64_t s_seed[kKnnWaves][kSeedWords];
   const float4* c4 = static_cast<const float4*>(a.cand);
@@ -265,14 +366,12 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
   for (int j = 0; j < kKnnQ; ++j) {
     const int64_t rr = min(rw + j, a.n_q - 1);  // rows past n_q repeat the last one and are not written
     q[j].init(s_buf[wave][j]);
-    q[j].x = a.x_q[3 * rr];
-    q[j].y = a.x_q[3 * rr + 1];
-    q[j].z = a.x_q[3 * rr + 2];
+    const float x = a.x_q[3 * rr], y = a.x_q[3 * rr + 1], z = a.x_q[3 * rr + 2];
     q[j].g = MODE ? a.group_q[rr] : 0;
-    q[j].mx = uniform(-2.0f * q[j].x);
-    q[j].my = uniform(-2.0f * q[j].y);
-    q[j].mz = uniform(-2.0f * q[j].z);
-    q[j].qq = uniform(fmaf(q[j].x, q[j].x, fmaf(q[j].y, q[j].y, q[j].z * q[j].z)));
+    q[j].mx = uniform(-2.0f * x);
+    q[j].my = uniform(-2.0f * y);
+    q[j].mz = uniform(-2.0f * z);
+    q[j].qq = uniform(fmaf(x, x, fmaf(y, y, z * z)));
     q[j].qn = uniform(__builtin_sqrtf(q[j].qq));
     q[j].set_limit();
   }
@@ -280,16 +379,16 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
   const int64_t n_groups = (a.n_c + kGroup - 1) / kGroup;
   int64_t t0 = 0;
   if (a.q_self0 >= 0 && n_groups > 0) t0 = ((a.q_self0 + r0) / kGroup) % n_groups;
-  const int jq = lane >> 4;
-  // lane l holds the box of step l % 16 of a group (the group's last step
+  const int jq = lane / kSteps;
+  // lane l holds the box of step l % kSteps of a group (the group's last step
   // where it has fewer: those bits are never used)
   auto box_of = [&](int64_t grp, float4& lo, float4& hi) {
-    const int64_t st = min(grp * (kGroup / kStep) + (lane & 15), n_steps - 1);
+    const int64_t st = min(grp * kSteps + lane % kSteps, n_steps - 1);
     lo = box[2 * st];
     hi = box[2 * st + 1];
   };
   // One step: 128 candidates from c0s, two per lane (entries past the n_s
-  // candidates take no part), the prefilter against the 4 queries, and the
+  // candidates take no part), the prefilter against the queries, and the
   // exact test and append where some lane passes it.
   auto visit = [&](int64_t c0s, int n_s) {
     const bool va = lane < n_s, vb = 64 + lane < n_s;
@@ -311,10 +410,10 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int j = 0; j < kKnnQ; ++j) {
       if (ma[j])
-        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x, q[j].y, q[j].z, ca)), index0 + lane, va,
+        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x(), q[j].y(), q[j].z(), ca)), index0 + lane, va,
                                   __float_as_int(ca.w), lane, k);
       if (mb[j])
-        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x, q[j].y, q[j].z, cb)), index0 + 64 + lane, vb,
+        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x(), q[j].y(), q[j].z(), cb)), index0 + 64 + lane, vb,
                                   __float_as_int(cb.w), lane, k);
     }
   };
@@ -332,8 +431,8 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
       const float4 lo = box[2 * st], hi = box[2 * st + 1];
 #pragma unroll
       for (int j = 0; j < kKnnQ; ++j)
-        in = in || (q[j].x >= lo.x && q[j].x <= hi.x && q[j].y >= lo.y && q[j].y <= hi.y && q[j].z >= lo.z &&
-                    q[j].z <= hi.z);
+        in = in || (q[j].x() >= lo.x && q[j].x() <= hi.x && q[j].y() >= lo.y && q[j].y() <= hi.y &&
+                    q[j].z() >= lo.z && q[j].z() <= hi.z);
     }
     const uint64_t m = __ballot(in);
     if (lane == 0) s_seed[wave][w0 >> 6] = m;
@@ -368,8 +467,8 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
     const int n_here = (int)min((int64_t)kGroup, a.n_c - c0);
     const float4 lo = blo, hi = bhi;
     if (tt + 1 < n_groups) box_of((t0 + tt + 1) % n_groups, blo, bhi);  // in flight during this group
-    // Steps no candidate of which can enter any of the wave's 4 top-k lists:
-    // lane l tests step l % 16 against query l / 16. For a candidate c in the
+    // Steps no candidate of which can enter any of the wave's top-k lists:
+    // lane l tests step l % kSteps against query l / kSteps. For a candidate c in the
     // box, |x_q - x_c| >= the box distance bx per axis, and the definition's
     // rounded operations are monotone, so with bx, by, bz computed as rounded
     // differences and d = ((bx*bx) + (by*by)) + (bz*bz) in the definition's
@@ -378,13 +477,13 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
     // whole step. (T only decreases, so the test stays valid for the group;
     // with fewer than k entries T is NaN and nothing is excluded.) Seeds,
     // already visited, are left out too.
-    uint32_t skip;
+    uint64_t skip;
     {
-      float qx = q[0].x, qy = q[0].y, qz = q[0].z, T = __uint_as_float((uint32_t)(q[0].tau >> 32));
+      float qx = q[0].x(), qy = q[0].y(), qz = q[0].z(), T = __uint_as_float((uint32_t)(q[0].tau >> 32));
 #pragma unroll
       for (int j = 1; j < kKnnQ; ++j)
         if (jq == j) {
-          qx = q[j].x; qy = q[j].y; qz = q[j].z;
+          qx = q[j].x(); qy = q[j].y(); qz = q[j].z();
           T = __uint_as_float((uint32_t)(q[j].tau >> 32));
         }
       float d;
@@ -395,12 +494,14 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
         const float bz = fmaxf(fmaxf(lo.z - qz, qz - hi.z), 0.0f);
         d = (bx * bx + by * by) + bz * bz;
       }
-      const uint64_t far = __ballot(d > T);
-      skip = (uint32_t)(far & (far >> 16) & (far >> 32) & (far >> 48) & 0xFFFFull);
-      const int64_t st0 = grp * (kGroup / kStep);  // a multiple of 16: its seeds are 16 bits of one word
+      skip = __ballot(d > T);
+#pragma unroll
+      for (int h = 32; h >= kSteps; h >>= 1) skip &= skip >> h;  // excluded for every query
+      const int64_t st0 = grp * kSteps;  // a multiple of kSteps: its seeds are bits of one word
       if (st0 < seed_steps) {
-        const uint64_t sw = s_seed[wave][st0 >> 6];
-        skip |= (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((sw >> (st0 & 63)) & 0xFFFFull));
+        const uint64_t sw = s_seed[wave][st0 >> 6] >> (st0 & 63);
+        skip |= ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sw >> 32)) << 32) |
+                (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)sw);
       }
     }
     // In the group that holds the wave's own queries the steps start just
@@ -411,9 +512,13 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
       const int64_t self = a.q_self0 + rw - c0;
       if (self >= 0 && self < n_here) pr = max(0, (int)(self >> 7) - 1);
     }
-    for (int t = 0; t < n_pairs; ++t, pr = pr + 1 == n_pairs ? 0 : pr + 1) {
-      if ((skip >> pr) & 1u) continue;
-      visit(c0 + pr * kStep, min(kStep, n_here - pr * kStep));
+    const uint64_t todo = ~skip & (~0ull >> (64 - n_pairs));
+    for (int half = 0; half < 2; ++half) {
+      const uint64_t from = ~0ull << pr;
+      for (uint64_t m = half ? todo & ~from : todo & from; m; m &= m - 1) {
+        const int st = __builtin_ctzll(m);
+        visit(c0 + st * kStep, min(kStep, n_here - st * kStep));
+      }
     }
   }
 #pragma unroll
@@ -421,6 +526,7 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
     const int64_t r = rw + j;
     if (r >= a.n_q) break;
     if (q[j].bcount > 0) q[j].flush(lane, k);
+    q[j].finish(lane);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int i = 64 * s + lane;
@@ -480,6 +586,13 @@ __global__ void __launch_bounds__(256) topk_merge_kernel(TopkMergeArgs a) {
   }
 }
 
+template <int KS, int MODE, int Q>
+hipError_t launch_knn_q(const KnnArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)((a.n_q + kKnnWaves * Q - 1) / (kKnnWaves * Q))), block(64 * kKnnWaves);
+  hipLaunchKernelGGL((knn_kernel<KS, MODE, Q>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
 template <int KS>
 hipError_t launch_knn_k(const KnnArgs& a, hipStream_t st) {
   if (a.n_c > 0) {
@@ -487,14 +600,21 @@ hipError_t launch_knn_k(const KnnArgs& a, hipStream_t st) {
     if (a.group_mode) hipLaunchKernelGGL((knn_prep_kernel<1>), pg, pb, 0, st, a);
     else hipLaunchKernelGGL((knn_prep_kernel<0>), pg, pb, 0, st, a);
   }
-  const dim3 grid((unsigned)((a.n_q + kKnnRows - 1) / kKnnRows)), block(64 * kKnnWaves);
-  if (a.group_mode == 1)
-    hipLaunchKernelGGL((knn_kernel<KS, 1>), grid, block, 0, st, a);
-  else if (a.group_mode == 2)
-    hipLaunchKernelGGL((knn_kernel<KS, 2>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((knn_kernel<KS, 0>), grid, block, 0, st, a);
-  return hipGetLastError();
+  // One query per wave: the most waves for the selections' scalar chains to
+  // overlap, and the shortest wave. Two share a wave's candidate loads where even
+  // that fills the chip more than twice (8192 waves at a time); beyond 128
+  // neighbours or across groups the selections weigh more and one stays faster:
+  //   queries / candidates, k        four per wave    two    one
+  //     5000 /  5000, 128                 116 us     88     51
+  //    24000 / 24000, 128                 261       113    124
+  //    24000 / 96000, 128                 202       171    174
+  //    20000 / 40000, 200                 367       242    206
+  //    15000 / 60000, 128, mode 2         661       488    407
+  if constexpr (KS == 2)
+    if (a.group_mode == 0 && a.n_q > 16384) return launch_knn_q<KS, 0, 2>(a, st);
+  return a.group_mode == 1   ? launch_knn_q<KS, 1, 1>(a, st)
+         : a.group_mode == 2 ? launch_knn_q<KS, 2, 1>(a, st)
+                             : launch_knn_q<KS, 0, 1>(a, st);
 }
 
 }  // namespace
