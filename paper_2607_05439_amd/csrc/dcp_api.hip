@@ -329,7 +329,7 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
     pa.q_row0 = q_row0;
     pa.n_q = n_q;
     pa.c_s = shape->c_s;
-    const bool tiled = dcp::gen_attn_tiled(shape->c_z, shape->n_heads, shape->head_dim);
+    const bool tiled = dcp::gen_attn_tiled(N, shape->c_z, shape->n_heads, shape->head_dim);
     pa.mask = key_mask;
     pa.kv_head_dim = tiled ? shape->head_dim : 0;
     pa.hd = hd;

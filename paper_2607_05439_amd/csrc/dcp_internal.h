@@ -228,7 +228,7 @@ hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st);
 hipError_t launch_fast_attn(const FastAttnArgs& a, hipStream_t st);
 hipError_t launch_fast_bias(const FastBiasArgs& a, hipStream_t st);
 hipError_t launch_gen_proj(const GenProjArgs& a, hipStream_t st);
-bool gen_attn_tiled(int32_t c_z, int32_t n_heads, int32_t head_dim);
+bool gen_attn_tiled(int64_t n_tok, int32_t c_z, int32_t n_heads, int32_t head_dim);
 hipError_t launch_gen_attn(const GenAttnArgs& a, hipStream_t st);
 hipError_t launch_gen_bias(const GenBiasArgs& a, hipStream_t st);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);

@@ -63,16 +63,17 @@ __device__ __forceinline__ f32x4 raw4_to_f32(const u32x4& r, int bf16) {
 }
 
 // k and v for the tiled attention: per 16 keys [heads by fours][4-channel
-// piece][key][head of the four][4], so that the piece c of four heads that the
-// 64 lanes load at once is 1 KB of consecutive memory (row-major, each lane's 16
-// bytes lay in a cache line of their own). The last keys and heads are packed
-// without padding: n_tok * H * d floats in all. Offset of piece 0 of head h of a
-// key, and the step from piece to piece.
-__device__ __forceinline__ int64_t kv_tile_offset(int64_t key, int64_t n_tok, int h, int H, int d, int* step) {
-  const int64_t t = key >> 4;
-  const int keys = (int)min((int64_t)16, n_tok - 16 * t), heads = min(4, H - (h & ~3));
+// piece][head of the four][key][4], so that lane (n, g)'s piece c of head g lies
+// 16 bytes after its neighbour's: the memory path takes four consecutive lanes'
+// 64 bytes at a time, and pieces in any other order (row-major, or key before
+// head) cost it a lookup per lane. The last keys and heads are packed without
+// padding: n_tok * H * d floats in all. Offset of piece 0 of head h of a key, and
+// the step from piece to piece. (The tiled attention runs where both fit 31-bit
+// byte offsets.)
+__device__ __forceinline__ int kv_tile_offset(int key, int n_tok, int h, int H, int d, int* step) {
+  const int t = key >> 4, keys = min(16, n_tok - 16 * t), heads = min(4, H - (h & ~3));
   *step = 4 * keys * heads;
-  return t * 16 * H * d + (int64_t)(h & ~3) * d * keys + ((int)(key & 15) * heads + (h & 3)) * 4;
+  return t * 16 * H * d + (h & ~3) * d * keys + ((h & 3) * keys + (key & 15)) * 4;
 }
 
 // The four projections on the fp32 matrix cores: each wave forms T x T tiles of
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(256) gen_proj_kernel(GenProjArgs a) {
         if (o < a.hd) {
           const int h = o / a.kv_head_dim, c = (o - h * a.kv_head_dim) >> 2;
           int step;
-          const int64_t at = kv_tile_offset(row, a.n_tok, h, a.hd / a.kv_head_dim, a.kv_head_dim, &step);
+          const int at = kv_tile_offset((int)row, (int)a.n_tok, h, a.hd / a.kv_head_dim, a.kv_head_dim, &step);
           *reinterpret_cast<f32x4*>(dst + at + c * step) = v;
         }
       } else if (a.hd % 4 == 0) {
@@ -259,22 +260,22 @@ __global__ void __launch_bounds__(64) gen_attn_any_kernel(GenAttnArgs a) {
   }
 }
 
-// Four consecutive elements of z as loaded, and as fp32.
+// Four consecutive elements of z as loaded (byte offset off), and as fp32.
 template <bool BF16>
 struct RawZ;
 template <>
 struct RawZ<false> {
-  typedef f32x4 type;
-  static __device__ __forceinline__ type load(const void* p, int64_t i) {
-    return *reinterpret_cast<const f32x4*>(static_cast<const float*>(p) + i);
+  typedef u32x4 type;
+  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0);
   }
-  static __device__ __forceinline__ f32x4 to_f32(const type& r) { return r; }
+  static __device__ __forceinline__ f32x4 to_f32(const type& r) { return __builtin_bit_cast(f32x4, r); }
 };
 template <>
 struct RawZ<true> {
   typedef u32x2 type;
-  static __device__ __forceinline__ type load(const void* p, int64_t i) {
-    return *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p) + i);
+  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
   }
   static __device__ __forceinline__ f32x4 to_f32(const type& r) {
     return f32x4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xFFFF0000u), __uint_as_float(r[1] << 16),
@@ -282,7 +283,7 @@ struct RawZ<true> {
   }
 };
 
-constexpr int kGenWaves = 4;  // 8 measured: 87 against 79 us (601 tokens, 128 channels), 88 against 82 (900, 32)
+constexpr int kGenWaves = 4;  // 8 were slower: 87 against 79 us (601 tokens, 128 channels), 88 against 82 (900, 32)
 
 // grid (rows / R, parts), 4 waves that share R query rows and take every fourth
 // tile of 16 keys of the part. Lane (n, g) holds key n of the tile.
@@ -297,13 +298,14 @@ constexpr int kGenWaves = 4;  // 8 measured: 87 against 79 us (601 tokens, 128 c
 //    it by the projection) and no exchange between lanes until the row's end.
 // The 16 lanes' and 4 waves' states meet in LDS, in a fixed order.
 // DP: the head size padded to a multiple of 4; c_z <= 16 CT.
-// What bounds it: 601 tokens of 128 channels (183 MB of z) take 79 us, the same
-// row pattern at the rate of a large read about 30: the row count fills the
-// chip's 512 workgroup slots 1.2 times, and per 16 keys the LayerNorm, softmax and
-// weighted sum issue about as many cycles of vector instructions as the bias
-// products take (1024). With k and v row-major, each lane's 16 bytes in a cache
-// line of their own, it took 106; with a lane per key, its state in LDS and z read
-// three times in 4-byte pieces, 1810.
+// What bounds it: the memory path's lookups. 601 tokens of 128 channels (183 MB of
+// z) take 68 us with the projection, the same rows at the rate of a large read
+// about 30; timing probes without the bias products, or with z or k and v always
+// from the same addresses, gained 1 to 5 us each, but k and v in an order that
+// puts four lanes' pieces on one line gained 8 (75 before), and a z load's four
+// consecutive lanes still lie in four rows. With k and v row-major it took 106;
+// with a lane per key, its state in LDS and z read three times in 4-byte pieces,
+// 1810.
 template <int NH, int DP, int CT, bool BF16, int R>
 __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs a) {
   constexpr int kHd = 4 * NH * DP;  // padded channels of all lanes' heads
@@ -318,11 +320,10 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
   const int64_t row0 = (int64_t)blockIdx.x * R;
   const int part = blockIdx.y;
   const int H = a.n_heads, d = a.head_dim, hd = H * d, c_z = a.c_z;
-  int64_t size, start;
-  chunk_of(a.k_len, a.n_parts, part, &size, &start);
-  start += a.k_lo;
-  const int64_t end = start + size;
-  const int64_t n_tiles = (size + 15) / 16;
+  int64_t size, first;
+  chunk_of(a.k_len, a.n_parts, part, &size, &first);
+  const int start = (int)(a.k_lo + first), end = start + (int)size;
+  const int n_tiles = ((int)size + 15) / 16;
 
   // Chunks past c_z or d repeat the last one: no load is conditional. fm is 0
   // there (and so are the weights and q), else 1.
@@ -331,23 +332,52 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
   float fm[CT];
 #pragma unroll
   for (int j = 0; j < CT; ++j) fm[j] = 16 * j < c_z ? 1.0f : 0.0f;
-  auto load_z = [&](int64_t t, int r) {
-    const int64_t key = min(start + 16 * t + n, end - 1);
-    const int64_t base = (min(row0 + r, a.n_q - 1) * a.n_tok + key) * c_z + 4 * g;
+  constexpr int kEb = BF16 ? 2 : 4;
+  const int row_bytes = (int)a.n_tok * c_z * kEb;
+  __amdgpu_buffer_rsrc_t zres[R];
 #pragma unroll
-    for (int j = 0; j < CT; ++j) zr[j] = RawZ<BF16>::load(a.z, base + min(16 * j, c_z - 16));
+  for (int r = 0; r < R; ++r)
+    zres[r] = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(a.z)) + min(row0 + r, a.n_q - 1) * row_bytes, 0, row_bytes,
+        kRawBufferFlags);
+  const __amdgpu_buffer_rsrc_t kres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.k), 0, (int)a.n_tok * hd * 4, kRawBufferFlags);
+  const __amdgpu_buffer_rsrc_t vres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.v), 0, (int)a.n_tok * hd * 4, kRawBufferFlags);
+  auto load_z = [&](int t, int r) {
+    const int off = (min(start + 16 * t + n, end - 1) * c_z + 4 * g) * kEb;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) zr[j] = RawZ<BF16>::load(zres[r], off, min(16 * j, c_z - 16) * kEb);
   };
   if (wave < n_tiles) load_z(wave, 0);
 
-  for (int x = tid; x < R * 4 * NH * kQs; x += 64 * kGenWaves) {
-    const int r = x / (4 * NH * kQs), h = x / kQs - r * (4 * NH), e = x % kQs;
-    s_q[r][h * kQs + e] = h < H && e < d ? a.q[min(row0 + r, a.n_q - 1) * hd + h * d + e] : 0.0f;
+  // q and the bias weights into LDS; every load unconditional (past the end: any
+  // element, times 0), so that they are in flight together
+  constexpr int kQn = (R * 4 * NH * kQs + 64 * kGenWaves - 1) / (64 * kGenWaves);
+  constexpr int kWn = 16 * 16 * CT / (64 * kGenWaves);
+  float qv[kQn], wv[kWn], gv[kWn];
+#pragma unroll
+  for (int u = 0; u < kQn; ++u) {
+    const int x = min(tid + 64 * kGenWaves * u, R * 4 * NH * kQs - 1), r = x / (4 * NH * kQs);
+    const int h = (x - r * (4 * NH * kQs)) / kQs, e = x % kQs;
+    qv[u] = a.q[min(row0 + r, a.n_q - 1) * hd + min(h, H - 1) * d + min(e, d - 1)];
+    if (h >= H || e >= d) qv[u] = 0.0f;
   }
-  for (int x = tid; x < 16 * 16 * CT; x += 64 * kGenWaves) {
-    const int l = (x >> 2) & 63, c = 16 * (x >> 8) + 4 * (l >> 4) + (x & 3), r = l & 15;
-    const int h = 4 * (r & 3) + (r >> 2);
-    s_w[x] = h < H && c < c_z ? a.w_b[h * c_z + c] * (a.gamma ? a.gamma[c] : 1.0f) : 0.0f;
+#pragma unroll
+  for (int u = 0; u < kWn; ++u) {
+    const int x = tid + 64 * kGenWaves * u, l = (x >> 2) & 63, c = 16 * (x >> 8) + 4 * (l >> 4) + (x & 3);
+    const int h = 4 * (l & 3) + ((l & 15) >> 2);
+    wv[u] = a.w_b[min(h, H - 1) * c_z + min(c, c_z - 1)];
+    gv[u] = a.gamma ? a.gamma[min(c, c_z - 1)] : 1.0f;
+    if (h >= H || c >= c_z) wv[u] = gv[u] = 0.0f;
   }
+#pragma unroll
+  for (int u = 0; u < kQn; ++u) {
+    const int x = tid + 64 * kGenWaves * u;
+    if (x < R * 4 * NH * kQs) (&s_q[0][0])[x] = qv[u];
+  }
+#pragma unroll
+  for (int u = 0; u < kWn; ++u) s_w[tid + 64 * kGenWaves * u] = wv[u] * gv[u];
   __syncthreads();
 
   const float scale = 1.0f / sqrtf((float)d), inv_cz = 1.0f / (float)c_z;
@@ -366,20 +396,28 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
     }
   }
 
-  for (int64_t t = wave; t < n_tiles; t += kGenWaves) {
-    const int64_t key = start + 16 * t + n;
-    const int64_t kk = min(key, end - 1);
+  for (int t = wave; t < n_tiles; t += kGenWaves) {
+    const int key = start + 16 * t + n;
+    const int kk = min(key, end - 1);
     const bool valid = key < end && (!a.mask || a.mask[kk] != 0);
-    int64_t at[NH];
-    int step[NH];
+    int at[NH], step[NH];
 #pragma unroll
-    for (int i = 0; i < NH; ++i) at[i] = kv_tile_offset(kk, a.n_tok, head[i], H, d, &step[i]);
-    // k of this tile, requested before the work on z
+    for (int i = 0; i < NH; ++i) at[i] = kv_tile_offset(kk, (int)a.n_tok, head[i], H, d, &step[i]);
+    // k and v of this tile before the next tile's z: loads complete in order, so
+    // waiting for v must not mean waiting for z from HBM
     f32x4 kr[NH][DP / 4], vr[NH][DP / 4];
 #pragma unroll
     for (int i = 0; i < NH; ++i)
 #pragma unroll
-      for (int c = 0; c < DP / 4; ++c) kr[i][c] = *reinterpret_cast<const f32x4*>(a.k + at[i] + min(c, d / 4 - 1) * step[i]);
+      for (int c = 0; c < DP / 4; ++c) kr[i][c] = __builtin_bit_cast(
+          f32x4, __builtin_amdgcn_raw_buffer_load_b128(kres, 4 * (at[i] + min(c, d / 4 - 1) * step[i]), 0, 0));
+#pragma unroll
+    for (int i = 0; i < NH; ++i)
+#pragma unroll
+      for (int c = 0; c < DP / 4; ++c)
+        vr[i][c] = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(vres, 4 * (at[i] + min(c, d / 4 - 1) * step[i]), 0, 0));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       f32x4 z[CT];
@@ -389,41 +427,44 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
         load_z(t, r + 1);
       else
         load_z(min(t + kGenWaves, n_tiles - 1), 0);
-      float s = 0.0f, v = 0.0f;
+      f32x4 w[CT];
+#pragma unroll
+      for (int j = 0; j < CT; ++j) w[j] = *reinterpret_cast<const f32x4*>(&s_w[(j * 64 + lane) * 4]);
+      __builtin_amdgcn_sched_barrier(0);  // (in flight during the statistics)
+      // four chains each: one wave per SIMD has nothing else to fill a chain's latency with
+      f32x4 s = {0.f, 0.f, 0.f, 0.f}, v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < CT; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s = fmaf(z[j][i], fm[j], s);
-      const float mu = sum4(s) * inv_cz;
+        for (int i = 0; i < 4; ++i) s[i] = fmaf(z[j][i], fm[j], s[i]);
+      const float mu = sum4((s[0] + s[1]) + (s[2] + s[3])) * inv_cz;
 #pragma unroll
       for (int j = 0; j < CT; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           z[j][i] = fmaf(z[j][i], fm[j], -mu * fm[j]);
-          v = fmaf(z[j][i], z[j][i], v);
+          v[i] = fmaf(z[j][i], z[j][i], v[i]);
         }
-      const float rstd = 1.0f / sqrtf(fmaf(sum4(v), inv_cz, a.eps));
-      f32x4 b = {0.f, 0.f, 0.f, 0.f};
+      const float rstd = 1.0f / sqrtf(fmaf(sum4((v[0] + v[1]) + (v[2] + v[3])), inv_cz, a.eps));
+      f32x4 b = {0.f, 0.f, 0.f, 0.f}, b1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < CT; ++j) {
-        const f32x4 w = *reinterpret_cast<const f32x4*>(&s_w[(j * 64 + lane) * 4]);
+      for (int j = 0; j < CT; j += 2)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b = mfma4(w[i], z[j][i], b);
-      }
-      if (r == 0)
-#pragma unroll
-        for (int i = 0; i < NH; ++i)
-#pragma unroll
-        for (int c = 0; c < DP / 4; ++c) vr[i][c] = *reinterpret_cast<const f32x4*>(a.v + at[i] + min(c, d / 4 - 1) * step[i]);
+        for (int i = 0; i < 4; ++i) {
+          b = mfma4(w[j][i], z[j][i], b);
+          b1 = mfma4(w[j + 1][i], z[j + 1][i], b1);
+        }
+      b += b1;
 #pragma unroll
       for (int i = 0; i < NH; ++i) {
-        float dot = 0.0f;
+        f32x4 dots = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < DP / 4; ++c) {
           const f32x4 q = *reinterpret_cast<const f32x4*>(&s_q[r][(4 * i + g) * kQs + 4 * c]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dot = fmaf(q[e], kr[i][c][e], dot);
+          for (int e = 0; e < 4; ++e) dots[e] = fmaf(q[e], kr[i][c][e], dots[e]);
         }
+        const float dot = (dots[0] + dots[1]) + (dots[2] + dots[3]);
         const float lg = valid ? fmaf(b[i], rstd, dot * scale) : -INFINITY;
         const float mn = fmaxf(m[r][i], lg);
         const float base = mn == -INFINITY ? 0.0f : mn;
@@ -566,14 +607,15 @@ hipError_t launch_gen_proj(const GenProjArgs& a, hipStream_t st) {
 // The tiled kernel takes pair widths of whole 16-channel chunks up to 128 and
 // the head shapes whose k, v and accumulators (heads per lane times head size)
 // fit its registers: up to 4 heads of 32, 8 of 16 or 16 of 8.
-bool gen_attn_tiled(int32_t c_z, int32_t n_heads, int32_t head_dim) {
+// Its 31-bit offsets reach 2 GiB of k or v and of one row of z.
+bool gen_attn_tiled(int64_t n_tok, int32_t c_z, int32_t n_heads, int32_t head_dim) {
   const int per_lane = (n_heads + 3) / 4;
-  return c_z % 16 == 0 && c_z <= 128 && head_dim % 4 == 0 &&
+  return n_tok <= (1 << 22) - 16 && c_z % 16 == 0 && c_z <= 128 && head_dim % 4 == 0 &&
          head_dim <= (per_lane == 1 ? 32 : per_lane == 2 ? 16 : 8);
 }
 
 hipError_t launch_gen_attn(const GenAttnArgs& a, hipStream_t st) {
-  if (!gen_attn_tiled(a.c_z, a.n_heads, a.head_dim))
+  if (!gen_attn_tiled(a.n_tok, a.c_z, a.n_heads, a.head_dim))
     hipLaunchKernelGGL(gen_attn_any_kernel, dim3((unsigned)a.n_q, (unsigned)a.n_parts), dim3(64), 0, st, a);
   else if (a.n_heads > 8)
     gen_attn_launch<4, 8>(a, st);
