@@ -26,7 +26,9 @@
 //                      the same way while this group computes. On this chip
 //                      every 1 KB LDS read also costs matrix-core issue time,
 //                      which is why each weight fragment serves two pair tiles.
-// fp32 path (any c_z <= 256, hidden <= 1024): one wave per pair, plain fp32.
+//   trans_split_kernel small pair counts: the waves of a workgroup share 32
+//                      pairs and split the hidden units.
+// The fp32 path is in transition_f32.hip.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -318,6 +320,144 @@ __global__ void __launch_bounds__(64 * kWaves) trans_kernel(TransArgs a) {
   wait_vm<0>();
 }
 
+// ----------------------------------------------------------------------------- few pairs
+// trans_kernel's time for one group is the chain of its 8 weight chunks through
+// LDS, about 23 us however few pairs there are, and 256 pairs per workgroup
+// leave most CUs idle. Here the waves of a workgroup share 32 pairs and split
+// the hidden units: wave w takes pairs of hidden tiles 2w and 2w + 1 (64
+// units), reads their weights straight from L2 (each 1 KB fragment once per
+// workgroup, 24 in flight) and the eight partial outputs are added in wave
+// order through LDS. Bound by the latency of those loads and of the two
+// exchanges: 2000 pairs 25.8 -> 11.7 us, 8192 pairs 26.0 -> 12.0 (the whole
+// call, weight preparation included).
+constexpr int kSplitPairs = 32;
+// Up to two rounds of workgroups over the 256 CUs: 16384 pairs take 19.7 us
+// against 26.0 with trans_kernel, a third round 27.7 against 26.1.
+constexpr int64_t kSplitMax = 2 * 256 * kSplitPairs;
+constexpr int kSplitTiles = kHt / 2 / kWaves;  // pairs of hidden tiles per wave
+__global__ void __launch_bounds__(64 * kWaves) trans_split_kernel(TransArgs a) {
+  __shared__ __attribute__((aligned(16))) f32x4 s_part[kWaves][16][64];  // 128 KB: [wave][ct, pair tile][lane]
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t pair0 = (int64_t)blockIdx.x * kSplitPairs;
+  const uint16_t* z_in = static_cast<const uint16_t*>(a.z_in);
+  u32x4 zz[2][4];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int64_t pr = min(pair0 + 16 * p + n, a.n_pairs - 1);  // pairs past the end are not stored
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) zz[p][ks] = *reinterpret_cast<const u32x4*>(z_in + pr * kCz + 32 * ks + 8 * g);
+  }
+  const char* wp = static_cast<const char*>(a.w_prep) + wave * kSplitTiles * kPairBytes + lane * 16;
+  // fragment r of a pair of hidden tiles, in the order of trans_kernel
+  auto frag = [&](int q, int r) {
+    const int off = r < 16 ? (r >> 3) * 8192 + (r & 1) * 4096 + ((r >> 1) & 3) * 1024 : 16384 + (r - 16) * 1024;
+    return *reinterpret_cast<const u32x4*>(wp + q * kPairBytes + off);
+  };
+  u32x4 wf[24];
+#pragma unroll
+  for (int r = 0; r < 24; ++r) wf[r] = frag(0, r);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // LayerNorm, by every wave for all 32 pairs (its own operands, no exchange)
+  bf16x8 nv[2][4];
+  {
+    float x[2][4][8], rstd[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      float s = 0.0f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t w = zz[p][ks][i >> 1];
+          x[p][ks][i] = __uint_as_float((i & 1) ? (w & 0xFFFF0000u) : (w << 16));
+          s += x[p][ks][i];
+        }
+      const float mu = sum4(s) * (1.0f / kCz);
+      float v = 0.0f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          x[p][ks][i] -= mu;
+          v = fmaf(x[p][ks][i], x[p][ks][i], v);
+        }
+      rstd[p] = __builtin_amdgcn_rsqf(sum4(v) * (1.0f / kCz) + a.eps);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const f32x4* gb = reinterpret_cast<const f32x4*>(a.gb_prep + 32 * ks + 8 * g);
+      const f32x4 gm[2] = {gb[0], gb[1]}, bt[2] = {gb[kCz / 4], gb[kCz / 4 + 1]};
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          nv[p][ks][i] = (__bf16)fmaf(x[p][ks][i] * rstd[p], gm[i >> 2][i & 3], bt[i >> 2][i & 3]);
+    }
+  }
+
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[8][2], h[2][2][2];
+#pragma unroll
+  for (int ct = 0; ct < 8; ++ct) acc[ct][0] = acc[ct][1] = zero;
+  bf16x8 hv[2];
+#pragma unroll
+  for (int q = 0; q < kSplitTiles; ++q)
+#pragma unroll
+    for (int r = 0; r < 24; ++r) {
+      const bf16x8 w = as_bf16x8(wf[r]);
+      if (q + 1 < kSplitTiles) wf[r] = frag(q + 1, r);
+      if (r < 16) {
+        const int tt = r >> 3, ks = (r >> 1) & 3, m = r & 1;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) h[m][tt][p] = mfma32(w, nv[p][ks], ks == 0 ? zero : h[m][tt][p]);
+      } else {
+        if (r == 16)  // h' as the B operand over the 32 units, as in trans_kernel
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const float x = h[0][j >> 2][p][j & 3];
+              hv[p][j] = (__bf16)(x * h[1][j >> 2][p][j & 3] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x)));
+            }
+#pragma unroll
+        for (int p = 0; p < 2; ++p) acc[r - 16][p] = mfma32(w, hv[p], acc[r - 16][p]);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // the next tiles' loads stay where they are
+    }
+#pragma unroll
+  for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) s_part[wave][2 * ct + p][lane] = acc[ct][p];
+  __syncthreads();
+
+  // wave w adds and stores channels 32 (w % 4) .. +31 of pair tile w / 4: lane
+  // (n, g) the 16 bytes of channels 32 ks + 8g .. +7. Every wave has read z
+  // before the barrier, so z_out may be z_in.
+  const int ks = wave & 3, p = wave >> 2;
+  const int64_t pr = pair0 + 16 * p + n;
+  if (pr >= a.n_pairs) return;
+  const u32x4 zr = *reinterpret_cast<const u32x4*>(z_in + pr * kCz + 32 * ks + 8 * g);
+  bf16x8 o;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    f32x4 sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = zr[2 * s + (i >> 1)];
+      sum[i] = __uint_as_float((i & 1) ? (w & 0xFFFF0000u) : (w << 16));
+    }
+    f32x4 part = s_part[0][2 * (2 * ks + s) + p][lane];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) part += s_part[w][2 * (2 * ks + s) + p][lane];
+    sum += part;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[4 * s + i] = (__bf16)sum[i];
+  }
+  *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.z_out) + pr * kCz + 32 * ks + 8 * g) = __builtin_bit_cast(u32x4, o);
+}
+
 }  // namespace
 
 size_t trans_prep_bytes() { return (size_t)kHt * kTileBytes + 2 * kCz * sizeof(float); }
@@ -327,6 +467,11 @@ hipError_t launch_transition(const TransArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(trans_prep_kernel, dim3((prep_threads + 255) / 256), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (a.n_pairs <= kSplitMax) {
+    hipLaunchKernelGGL(trans_split_kernel, dim3((unsigned)((a.n_pairs + kSplitPairs - 1) / kSplitPairs)),
+                       dim3(64 * kWaves), 0, st, a);
+    return hipGetLastError();
+  }
   const int64_t n_groups = (a.n_pairs + kGroupPairs - 1) / kGroupPairs;
   const int64_t grid = n_groups < 256 ? n_groups : 256;  // one persistent workgroup per CU
   hipLaunchKernelGGL(trans_kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, a);

@@ -89,6 +89,27 @@ def test_bf16_ragged_inplace_deterministic():
     run(dev(flat), w, DCP_BF16, n_pairs=0)
 
 
+@pytest.mark.parametrize("n", [1, 16, 17, 31, 33, 16383, 16384, 16385])
+def test_bf16_split_kernel_edges(n):
+    """Pair counts around the 16-pair tiles and 32-pair workgroups of the kernel
+    for few pairs, and on both sides of the rule that chooses it: against the
+    oracle (bf16 operands and output: the 1e-2 bound), in place, the pairs past
+    n untouched."""
+    import torch
+    wl, hidden = synth.transition_workload("trans192_bf16")
+    w = synth.transition_weights(wl, hidden, affine=True)
+    flat = synth.z_host(wl, range(n // 192 + 1)).reshape(-1, 128)
+    zt = dev(flat)
+    got = run(zt, w, DCP_BF16, n_pairs=n)
+    some = np.unique(np.r_[np.arange(min(n, 64)), np.arange(max(0, n - 300), n)])
+    ref = oracle.transition(flat[some], w["w1"], w["w2"], w["w3"], w["gamma"], w["beta"])
+    assert rel_err(host_f64(got[torch.from_numpy(some).to("cuda:0")]), ref) <= 1e-2
+    zc = zt.clone()
+    run(zc, w, DCP_BF16, n_pairs=n, in_place=True)
+    assert torch.equal(zc[:n], got[:n])
+    assert torch.equal(zc[n:], zt[n:])
+
+
 def test_bf16_full_size_in_place_sampled():
     """The 24000-token pair tensor (147 GB, bf16) updated in place in one call,
     as the benchmark does; sampled pairs against the oracle on the generator's
