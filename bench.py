@@ -783,8 +783,8 @@ def attention_main(args, wl):
     synth.device_read(z.data_ptr(), read_bytes, sink.data_ptr(), sp)
     hip.record(e1, sp)
     read_gbps = read_bytes / (hip.elapsed_ms(e0, e1) * 1e-3) / 1e9
-    # the attention kernel's own z stream over the first stripe (same grid, loads
-    # and ring), no arithmetic
+    # a z stream of the attention kernel's loads over the first stripe (64 rows per
+    # workgroup, a deeper ring), no arithmetic
     pattern_gbps = pattern_ms = None
     if wl.bf16 and cz == 128:
         q0, nq = wl.stripes[0]

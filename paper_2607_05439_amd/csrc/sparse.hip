@@ -52,11 +52,14 @@ constexpr float kShift = 192.0f;
 // ----------------------------------------------------------------------------- projections
 constexpr int kProjTiles = 4;  // 16-atom tiles per wave (share the weight operands)
 
-// Any c_atom (a multiple of 32). grid (groups of 4 tiles of 16 atoms, head h,
-// projection {q, k, v, g}); one wave each. Weight rows of head h are the A
-// operand (rows e = 16 et + n), the atoms the B operand: the accumulator holds
-// outputs 16 et + 4g + i of atom n.
+// Any c_atom (a multiple of 32), known (C) or not (0). grid (groups of 4 tiles of
+// 16 atoms, head h, projection {q, k, v, g}); one wave each. Weight rows of head
+// h are the A operand (rows e = 16 et + n), the atoms the B operand: the
+// accumulator holds outputs 16 et + 4g + i of atom n.
+template <int C>
 __global__ void __launch_bounds__(64) atom_proj_kernel(SparseProjArgs a) {
+  const int c_atom = C ? C : a.c_atom;
+  constexpr int kSteps = C ? C / 32 : 1;  // k-steps whose loads go out together
   const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
   const int h = blockIdx.y, which = blockIdx.z;  // 0 q, 1 k, 2 v, 3 g
   const bool is_query = (which == 0 || which == 3);
@@ -70,16 +73,17 @@ __global__ void __launch_bounds__(64) atom_proj_kernel(SparseProjArgs a) {
 #pragma unroll
   for (int u = 0; u < kProjTiles; ++u) {
     const int64_t row = min((tile0 + u) * 16 + n, rows - 1);  // rows past the end are not stored
-    arow[u] = a.a + (base + row) * a.c_atom + 8 * g;
+    arow[u] = a.a + (base + row) * c_atom + 8 * g;
   }
   f32x4 acc[kProjTiles][2];
 #pragma unroll
   for (int u = 0; u < kProjTiles; ++u) acc[u][0] = acc[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < a.c_atom; k0 += 32) {
+#pragma unroll kSteps
+  for (int k0 = 0; k0 < c_atom; k0 += 32) {
     bf16x8 whi[2], wlo[2];
 #pragma unroll
     for (int et = 0; et < 2; ++et) {
-      const float4* wp = reinterpret_cast<const float4*>(w + (int64_t)(h * kD + 16 * et + n) * a.c_atom + k0 + 8 * g);
+      const float4* wp = reinterpret_cast<const float4*>(w + (int64_t)(h * kD + 16 * et + n) * c_atom + k0 + 8 * g);
       const float4 x0 = wp[0], x1 = wp[1];
       const float xs[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
@@ -347,8 +351,10 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
   return __builtin_amdgcn_fdot2_f32_bf16(as_bf16x2(a), as_bf16x2(b), c, false);
 }
 
-template <bool kBf16, int KMAX>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kBf16 && KMAX == 128 ? 5 : 1)))
+// kUnroll: K (and V) loads per lane per batch (2, so that more waves fit; 4 where
+// there are few queries)
+template <bool kBf16, int KMAX, int kUnroll>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kBf16 && KMAX == 128 && kUnroll == 2 ? 5 : 1)))
 sparse_attn_kernel(SparseAttnArgs a) {
   constexpr int EB = kBf16 ? 2 : 4;  // bytes per element of P, K and V
   constexpr int EPL = 16 / EB;       // K/V elements per lane per 16-byte load
@@ -356,8 +362,7 @@ sparse_attn_kernel(SparseAttnArgs a) {
   constexpr int NPI = 64 / LPN;      // rows per load instruction (4 | 2)
   constexpr int LPH = kD / EPL;      // lanes per head (4 | 8)
   constexpr int KS = KMAX / 64;      // slots per lane in slot order
-  constexpr int kUnroll = 2;         // K (and V) loads per lane per batch (few: more waves fit)
-  constexpr int kBatch = NPI * kUnroll;  // slots per batch (8 | 4)
+  constexpr int kBatch = NPI * kUnroll;  // slots per batch
   constexpr int kPad = 32;           // list length granularity
   constexpr int kPasses = KMAX / 16; // bias passes of 16 slots
   static_assert(kPad % 16 == 0 && kPad % kBatch == 0 && KMAX % kPad == 0, "list padding");
@@ -715,18 +720,40 @@ sparse_attn_kernel(SparseAttnArgs a) {
   }
 }
 
-template <bool kBf16, int KMAX>
+template <bool kBf16, int KMAX, int kUnroll>
 hipError_t launch_attn(const SparseAttnArgs& a, hipStream_t st) {
   const int64_t n_wg = (a.n_q + kWaves - 1) / kWaves;
   const int64_t grid = (n_wg + 7) / 8 * 8;
-  hipLaunchKernelGGL((sparse_attn_kernel<kBf16, KMAX>), dim3((unsigned)grid), dim3(64 * kWaves), 0, st, a);
+  hipLaunchKernelGGL((sparse_attn_kernel<kBf16, KMAX, kUnroll>), dim3((unsigned)grid), dim3(64 * kWaves), 0, st, a);
   return hipGetLastError();
+}
+
+// Up to 2048 queries there are at most two waves per SIMD, so nothing hides a
+// wave's chain of batches and registers are free: batches twice as long (500 to
+// 2000 queries, whole calls: 128 slots 16.3 -> 15.4 us, 200 slots 29.4 -> 27.5, fp32
+// 22.2 -> 20.0; four times as long gains no more). With more queries the other
+// waves hide it: 5000 queries 34.1 against 35.7, 24000 130 against 133.
+template <int KMAX>
+hipError_t launch_attn_width(const SparseAttnArgs& a, bool bf16, hipStream_t st) {
+  if (a.n_q <= 2048) return bf16 ? launch_attn<true, KMAX, 4>(a, st) : launch_attn<false, KMAX, 4>(a, st);
+  return bf16 ? launch_attn<true, KMAX, 2>(a, st) : launch_attn<false, KMAX, 2>(a, st);
 }
 
 }  // namespace
 
 hipError_t launch_sparse_proj(const SparseProjArgs& a, hipStream_t st) {
   const int64_t rows = a.n_atoms > a.n_q ? a.n_atoms : a.n_q;
+  // Few atoms: a workgroup of atom_proj128_kernel converts a whole weight matrix
+  // before its first product, and 1000 atoms give it 16 workgroups. One wave per 64
+  // atoms and head, with all its loads in flight at once, gives the same bits
+  // sooner: whole calls of 1000 atoms 23.9 -> 16.3 us, 4000 33.7 -> 28.5, 8000 52.8
+  // -> 50.5. It reads the weights once per 64 atoms, so 16000 lose: 35.1 -> 37.7.
+  constexpr int64_t kFewAtoms = 8192;
+  if (a.c_atom == kHD && rows <= kFewAtoms) {
+    const int64_t groups = ((rows + 15) / 16 + kProjTiles - 1) / kProjTiles;
+    hipLaunchKernelGGL(atom_proj_kernel<kHD>, dim3((unsigned)groups, kH, 4), dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
   if (a.c_atom == kHD) {
     int64_t wgs = ((rows + 63) / 64 + 3) / 4;
     if (wgs > 128) wgs = 128;  // 4 x 128 workgroups, two per CU (64 KB of LDS each); waves loop over atom groups
@@ -734,13 +761,12 @@ hipError_t launch_sparse_proj(const SparseProjArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   const int64_t groups = ((rows + 15) / 16 + kProjTiles - 1) / kProjTiles;
-  hipLaunchKernelGGL(atom_proj_kernel, dim3((unsigned)groups, kH, 4), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(atom_proj_kernel<0>, dim3((unsigned)groups, kH, 4), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_sparse_attn(const SparseAttnArgs& a, bool bf16, hipStream_t st) {
-  if (a.k_slots <= 128) return bf16 ? launch_attn<true, 128>(a, st) : launch_attn<false, 128>(a, st);
-  return bf16 ? launch_attn<true, 256>(a, st) : launch_attn<false, 256>(a, st);
+  return a.k_slots <= 128 ? launch_attn_width<128>(a, bf16, st) : launch_attn_width<256>(a, bf16, st);
 }
 
 }  // namespace dcp

@@ -508,8 +508,8 @@ def device_copy(src: int, dst: int, nbytes: int, stream: int) -> None:
 
 
 def device_read_pattern(z: int, n_tok: int, n_rows: int, n_parts: int, sink: int, stream: int) -> None:
-    """Reads the 256-B pair vectors of z rows [0, n_rows) in the fused attention
-    kernel's order, with no arithmetic (the access pattern's bandwidth ceiling)."""
+    """Reads the 256-B pair vectors of z rows [0, n_rows) with the fused attention
+    kernel's loads and no arithmetic (the access pattern's bandwidth ceiling)."""
     if _dev().synth_dev_read_pattern(z, n_tok, n_rows, n_parts, sink, stream) != 0:
         raise RuntimeError("synth_dev_read_pattern failed")
 

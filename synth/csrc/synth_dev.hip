@@ -112,10 +112,11 @@ __global__ void __launch_bounds__(256) read_kernel(const uint4* __restrict__ src
   if (acc == 0x9E3779B9u) sink[0] = acc;  // practically never taken; keeps the loads
 }
 
-// Reads 256-byte pair vectors of rows [0, n_rows) the way the fused attention
-// kernel streams them, with no arithmetic: the memory system's ceiling for that
-// stream. Same geometry and instructions: workgroups of 4 waves, each wave 16
-// rows over one of n_parts key ranges, one workgroup per CU (160 KB of LDS),
+// Reads 256-byte pair vectors of rows [0, n_rows) with the fused attention
+// kernel's loads and no arithmetic: the memory system's ceiling for such a
+// stream. Its own geometry is the one that streams best alone: workgroups of 4
+// waves, each wave 16 rows over one of n_parts key ranges, one workgroup per CU
+// (160 KB of LDS),
 // every key fetched as four non-temporal direct-to-LDS loads of 4 rows x 256 B
 // under one M0 into an 8-slot ring per wave, issued 7 keys ahead; each key is
 // read back from LDS once (folded into a word so the reads stay live).
@@ -146,7 +147,7 @@ __global__ void __launch_bounds__(256, 1) read_pattern_kernel(const uint16_t* __
   __shared__ u32x4 ring[4][kPatRing][256];    // 128 KB: 4 KB per key and wave
   __shared__ uint32_t fill[32 * 256 - 16];    // the rest of the CU's LDS
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // workgroup -> (64-row group, part) as the attention numbers them: row
+  // workgroup -> (64-row group, part): row
   // groups fastest, or (xcd_order) XCD x walking the groups x mod 8 part by
   // part from part x mod n_parts
   int64_t rg, p;
@@ -260,7 +261,7 @@ int synth_dev_copy(const void* src, void* dst, int64_t bytes, void* stream) {
 int synth_dev_read_pattern(const void* z, int64_t n_tok, int64_t n_rows, int32_t n_parts, void* sink, void* stream) {
   if (!z || !sink || n_tok <= 0 || n_rows <= 0 || n_parts < 1 || n_parts > n_tok) return -1;
   if (n_tok * 256 * 16 + 4096 > INT32_MAX) return -1;  // 32-bit buffer offsets of 16 rows
-  // the attention's workgroup order: per XCD from 256 row groups and two parts on
+  // workgroup order: per XCD from 256 row groups and two parts on
   const int64_t n_rg = (n_rows + 63) / 64;
   const int xcd_order = n_rg >= 256 && n_parts > 1;
   if (xcd_order)

@@ -159,3 +159,38 @@ def test_f32_gathered_and_k256():
     err = rel_err(got, ref)
     log(f"  atoms200_f32 k=256 gathered rel err {err:.3e}")
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,k", [("bf16", 100), ("bf16", 200), ("f32", 100), ("f32", 200)])
+def test_few_atoms_and_few_queries(dtype, k):
+    """Both sides of the rules for few atoms (8192) and few queries (2048), and
+    ragged ends of their 64-atom groups: bf16 rows are the same bits whichever
+    kernels serve them; fp32 batches differ in the order of their running maxima, so
+    those rows agree to a few fp32 roundings of sums of k terms (2e-6)."""
+    import torch
+    import paper_2607_05439_amd as dcp
+    code, dt = (DCP_BF16, torch.bfloat16) if dtype == "bf16" else (DCP_F32, torch.float32)
+    g = torch.Generator(device="cuda:0").manual_seed(k)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    n_max, q_max = 8193, 2049
+    held = [rnd(128, 128) / 128 ** 0.5 for _ in range(4)] + [rnd(4, 16) / 4, rnd(4), 1 + rnd(16) / 4, rnd(16) / 4]
+    w = dcp.make_weights(*held)  # the struct holds their addresses
+    s, p = rnd(n_max, 128).to(dt), rnd(q_max, k, 16).to(dt)
+
+    def call(n, rows, nbr):
+        shape = dcp.make_sparse_shape(n, 128, 16, 4, 32, k, code, code, 1, 1e-5)
+        ws = torch.empty(max(dcp.dcp_sparse_workspace_size(shape, rows), 256), dtype=torch.uint8, device="cuda:0")
+        out = torch.empty((rows, 128), dtype=dt, device="cuda:0")
+        dcp.dcp_sparse_pair_bias_attention(shape, w, s[:n], p[:rows].contiguous(), nbr[:rows].contiguous(), 0, rows, 1,
+                                           out, ws, ws.numel())
+        return out.float()
+
+    for n in (8191, 8192, 2049):  # the neighbours lie in the first n atoms of either call
+        nbr = torch.randint(-1, n, (q_max, k), generator=g, device="cuda:0", dtype=torch.int32)
+        ref = call(n_max, q_max, nbr)
+        for rows in (q_max, 2048, 65):
+            got = call(n, rows, nbr)
+            if dtype == "bf16":
+                assert torch.equal(got, ref[:rows])
+            else:
+                assert ((got - ref[:rows]).norm() / ref[:rows].norm()).item() <= 2e-6
