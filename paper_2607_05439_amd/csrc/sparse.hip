@@ -732,11 +732,19 @@ hipError_t launch_attn(const SparseAttnArgs& a, hipStream_t st) {
 // wave's chain of batches and registers are free: batches twice as long (500 to
 // 2000 queries, whole calls: 128 slots 16.3 -> 15.4 us, 200 slots 29.4 -> 27.5, fp32
 // 22.2 -> 20.0; four times as long gains no more). With more queries the other
-// waves hide it: 5000 queries 34.1 against 35.7, 24000 130 against 133.
+// waves hide it: 5000 queries 34.1 against 35.7, 24000 130 against 133. The bf16
+// kernel of up to 256 slots has as many registers, and waves, either way: the longer
+// batches serve it at any size (200 slots, 24000 of 48000 atoms 198.6 -> 191.8 us, 6000
+// 61.8 -> 59.6; fp32 92 against 93).
 template <int KMAX>
 hipError_t launch_attn_width(const SparseAttnArgs& a, bool bf16, hipStream_t st) {
-  if (a.n_q <= 2048) return bf16 ? launch_attn<true, KMAX, 4>(a, st) : launch_attn<false, KMAX, 4>(a, st);
-  return bf16 ? launch_attn<true, KMAX, 2>(a, st) : launch_attn<false, KMAX, 2>(a, st);
+  const bool few = a.n_q <= 2048;
+  if (bf16) {
+    if constexpr (KMAX == 128)
+      if (!few) return launch_attn<true, KMAX, 2>(a, st);
+    return launch_attn<true, KMAX, 4>(a, st);
+  }
+  return few ? launch_attn<false, KMAX, 4>(a, st) : launch_attn<false, KMAX, 2>(a, st);
 }
 
 }  // namespace
