@@ -1,5 +1,5 @@
 // CDNA4 (gfx950) building blocks shared by the fused kernels: vector types,
-// matrix-core wrappers and cross-lane exchanges.
+// matrix-core wrappers, cross-lane exchanges and the bias-tile transpose.
 //
 // Matrix-core layouts (64 lanes, lane L, n = L % 16, g = L / 16):
 // v_mfma_f32_16x16x32_bf16: A holds row n, k-slots 8g..8g+7; B holds column n,
@@ -61,6 +61,26 @@ __device__ __forceinline__ float max4(float x) {
   b = x;
   swap16(a, b);
   return fmaxf(a, b);
+}
+
+// b[k][i] holds (row n, head 4g+i, key k) for the tile's 16 keys. After this,
+// b[4a + r][i] holds (row n, head 4a+i, key 4g+r): the QK^T accumulator layout
+// of head 4a+i. A 4x4 exchange of 4x4 blocks between the lane groups, done
+// with two rounds of cross-lane swaps (bit 1 of the group, then bit 0). In
+// registers alone; attn_kernel, whose waves split the keys, makes it through LDS.
+__device__ __forceinline__ void transpose_bias(float (&b)[16][4]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) swap32(b[4 * c + r][i], b[4 * (c + 2) + r][i]);
+#pragma unroll
+  for (int c = 0; c < 4; c += 2)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) swap16(b[4 * c + r][i], b[4 * (c + 1) + r][i]);
 }
 
 // ---- direct-to-LDS loads and explicit waits

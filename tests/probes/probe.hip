@@ -46,25 +46,6 @@ __global__ void __launch_bounds__(64) k_swaps(float* out) {
   out[L * 6 + 5] = max4((float)((L * 37) % 64));
 }
 
-// b[k][i] holds (row n, head 4g+i, key k) for the tile's 16 keys. After this,
-// b[4a + r][i] holds (row n, head 4a+i, key 4g+r): the QK^T accumulator layout
-// of head 4a+i. A 4x4 exchange of 4x4 blocks between the lane groups, done
-// with two rounds of cross-lane swaps (bit 1 of the group, then bit 0).
-__device__ __forceinline__ void transpose_bias(float (&b)[16][4]) {
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) swap32(b[4 * c + r][i], b[4 * (c + 2) + r][i]);
-#pragma unroll
-  for (int c = 0; c < 4; c += 2)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) swap16(b[4 * c + r][i], b[4 * (c + 1) + r][i]);
-}
-
 __global__ void __launch_bounds__(64) k_transpose(float* out) {
   const int L = threadIdx.x;
   float b[16][4];

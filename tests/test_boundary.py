@@ -378,3 +378,14 @@ def test_noalloc_rejects_beyond_its_scratch():
     # the workloads it is meant for fit: a 1024-token layer, a 3000-row stripe of 12000 tokens
     assert dcp.dcp_workspace_size(shape(n_tokens=1024), 1024, 4) <= dcp.NOALLOC_SCRATCH_BYTES
     assert dcp.dcp_workspace_size(shape(n_tokens=12000), 3000, 4) <= dcp.NOALLOC_SCRATCH_BYTES
+
+
+def test_layout_probes_check_the_librarys_own_helpers():
+    """The lane-layout probes compile against the library's device header: every helper they check
+    is defined there, none in the probes themselves, where it would be code that only a test runs."""
+    probe = open(os.path.join(ROOT, "tests", "probes", "probe.hip")).read()
+    header = open(os.path.join(ROOT, "paper_2607_05439_amd", "csrc", "cdna4.h")).read()
+    define = r"__device__\s+__forceinline__\s+[\w ]+?\b(\w+)\("
+    assert re.findall(define, probe) == []
+    used = [n for n in re.findall(define, header) if re.search(rf"\b{n}(<\d+>)?\(", probe)]
+    assert set(used) >= {"mfma32", "mfma16", "swap32", "swap16", "sum4", "max4", "transpose_bias", "dma_b128"}
