@@ -126,13 +126,10 @@ struct QueryTopk {
   int count, bcount;
   uint64_t* buf;
   int32_t g;
-  float mx, my, mz;  // -2 x, -2 y, -2 z (exact, as is halving them back)
+  float x, y, z;
+  float mx, my, mz;  // -2 x, -2 y, -2 z (infinite beyond half the largest float: for the prefilter only)
   float qq, qn;      // |q|^2 and |q|
   float lim;         // prefilter bound on |c|^2 - 2 c.q for candidates that may still enter
-
-  __device__ __forceinline__ float x() const { return -0.5f * mx; }
-  __device__ __forceinline__ float y() const { return -0.5f * my; }
-  __device__ __forceinline__ float z() const { return -0.5f * mz; }
 
   // The prefilter computes e = |c|^2 - 2 c.q with three multiply-adds; the
   // exact distance is |c - q|^2 = e + |q|^2 up to rounding. If the rounded
@@ -368,6 +365,9 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
     q[j].init(s_buf[wave][j]);
     const float x = a.x_q[3 * rr], y = a.x_q[3 * rr + 1], z = a.x_q[3 * rr + 2];
     q[j].g = MODE ? a.group_q[rr] : 0;
+    q[j].x = uniform(x);
+    q[j].y = uniform(y);
+    q[j].z = uniform(z);
     q[j].mx = uniform(-2.0f * x);
     q[j].my = uniform(-2.0f * y);
     q[j].mz = uniform(-2.0f * z);
@@ -410,10 +410,10 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int j = 0; j < kKnnQ; ++j) {
       if (ma[j])
-        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x(), q[j].y(), q[j].z(), ca)), index0 + lane, va,
+        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x, q[j].y, q[j].z, ca)), index0 + lane, va,
                                   __float_as_int(ca.w), lane, k);
       if (mb[j])
-        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x(), q[j].y(), q[j].z(), cb)), index0 + 64 + lane, vb,
+        q[j].template offer<MODE>(__float_as_uint(dist2(q[j].x, q[j].y, q[j].z, cb)), index0 + 64 + lane, vb,
                                   __float_as_int(cb.w), lane, k);
     }
   };
@@ -431,8 +431,8 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
       const float4 lo = box[2 * st], hi = box[2 * st + 1];
 #pragma unroll
       for (int j = 0; j < kKnnQ; ++j)
-        in = in || (q[j].x() >= lo.x && q[j].x() <= hi.x && q[j].y() >= lo.y && q[j].y() <= hi.y &&
-                    q[j].z() >= lo.z && q[j].z() <= hi.z);
+        in = in || (q[j].x >= lo.x && q[j].x <= hi.x && q[j].y >= lo.y && q[j].y <= hi.y &&
+                    q[j].z >= lo.z && q[j].z <= hi.z);
     }
     const uint64_t m = __ballot(in);
     if (lane == 0) s_seed[wave][w0 >> 6] = m;
@@ -479,11 +479,11 @@ __global__ void __launch_bounds__(64 * kKnnWaves) __attribute__((amdgpu_waves_pe
     // already visited, are left out too.
     uint64_t skip;
     {
-      float qx = q[0].x(), qy = q[0].y(), qz = q[0].z(), T = __uint_as_float((uint32_t)(q[0].tau >> 32));
+      float qx = q[0].x, qy = q[0].y, qz = q[0].z, T = __uint_as_float((uint32_t)(q[0].tau >> 32));
 #pragma unroll
       for (int j = 1; j < kKnnQ; ++j)
         if (jq == j) {
-          qx = q[j].x(); qy = q[j].y(); qz = q[j].z();
+          qx = q[j].x; qy = q[j].y; qz = q[j].z;
           T = __uint_as_float((uint32_t)(q[j].tau >> 32));
         }
       float d;

@@ -203,3 +203,16 @@ def test_two_queries_per_wave(k, lattice):
     rows = np.concatenate([np.arange(0, n_q, 97), [n_q - 2, n_q - 1]])
     ri, rd = oracle.knn(q[rows], x, k)
     same((got[0][rows], got[1][rows]), (np.where(ri < 0, ri, ri + 5), rd), "against the oracle")
+
+
+@pytest.mark.parametrize("k", [3, 200])
+def test_coordinates_beyond_half_the_largest_float(k):
+    """Coordinates whose double is infinite in fp32: differences of such neighbours are ordinary
+    numbers (or 0 at the same point), and squares of the others overflow to +inf, which ties."""
+    x = np.random.default_rng(k).standard_normal((300, 3)).astype(np.float32)
+    x[100:] *= np.float32(0.7e38)  # up to about 2.4e38, half of them beyond 1.7e38 in some coordinate
+    x[[7, 8, 290]] = 2e38
+    x[9], x[291] = np.float32(3.4e38), np.float32(-3.4e38)
+    got = gpu_knn(x, x, k, q_self0=0)
+    assert got[0][7][:3].tolist() == [7, 8, 290] and (got[1][7][:3] == 0).all()
+    same(got, oracle.knn(x, x, k), "beyond half the largest float")
