@@ -216,3 +216,43 @@ def test_coordinates_beyond_half_the_largest_float(k):
     got = gpu_knn(x, x, k, q_self0=0)
     assert got[0][7][:3].tolist() == [7, 8, 290] and (got[1][7][:3] == 0).all()
     same(got, oracle.knn(x, x, k), "beyond half the largest float")
+
+
+@pytest.mark.parametrize("k", [1, 64, 100, 128, 200, 256])
+def test_shared_kth_distances(k):
+    """Padding atoms at one point, a coarse lattice and both: the k-th distance is shared by more
+    candidates than the list holds, and the smaller indices win, up to the largest index there is."""
+    r = np.random.default_rng(k)
+    pad = np.zeros((700, 3), np.float32)
+    grid = r.integers(0, 4, (700, 3)).astype(np.float32)
+    for x, index0 in ((pad, 0), (grid, 2**31 - 1 - 700), (np.concatenate([grid, pad, grid[::-1]]), 12345)):
+        ri, rd = oracle.knn(x, x, k)
+        got = gpu_knn(x, x, k, c_index0=index0, q_self0=0)
+        same(got, (np.where(ri < 0, ri, ri + index0), rd), f"{len(x)} candidates from index {index0}")
+
+
+def test_shared_distances_take_no_longer():
+    """Atoms at one point enter a full list no more often than atoms in general position: a candidate
+    at the k-th distance with a larger index is turned away before the selection (when it was not,
+    these calls took five times as long as the others; the bound is twice)."""
+    import torch
+    import paper_2607_05439_amd as dcp
+    n, k = 4800, 128
+    ws_bytes = dcp.dcp_knn_workspace_size(n)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda:0")
+    idx = torch.empty((n, k), dtype=torch.int32, device="cuda:0")
+
+    def us(x):
+        best = float("inf")
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            dcp.dcp_knn_topk(x, n, x, n, 0, 0, None, None, 0, k, idx, None, ws, ws_bytes)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        return best
+
+    one, spread = us(torch.zeros((n, 3), device="cuda:0")), us(30 * torch.randn((n, 3), device="cuda:0"))
+    log(f"case {n} atoms, k = {k}: at one point {one:.1f} us, in general position {spread:.1f} us")
+    assert one <= 2 * spread
