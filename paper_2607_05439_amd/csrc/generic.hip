@@ -400,9 +400,15 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
     const int key = start + 16 * t + n;
     const int kk = min(key, end - 1);
     const bool valid = key < end && (!a.mask || a.mask[kk] != 0);
-    int at[NH], step[NH];
+    // lanes past the part's end read k and v out of range, zeros: the last key's own,
+    // times a weight of 0, would turn an infinite v into a NaN
+    uint32_t at[NH];  // byte offset of piece 0
+    int step[NH];
 #pragma unroll
-    for (int i = 0; i < NH; ++i) at[i] = kv_tile_offset(kk, (int)a.n_tok, head[i], H, d, &step[i]);
+    for (int i = 0; i < NH; ++i) {
+      const int x = kv_tile_offset(kk, (int)a.n_tok, head[i], H, d, &step[i]);
+      at[i] = key < end ? 4u * (uint32_t)x : (uint32_t)kOutOfRange;
+    }
     // k and v of this tile before the next tile's z: loads complete in order, so
     // waiting for v must not mean waiting for z from HBM
     f32x4 kr[NH][DP / 4], vr[NH][DP / 4];
@@ -410,13 +416,14 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
     for (int i = 0; i < NH; ++i)
 #pragma unroll
       for (int c = 0; c < DP / 4; ++c) kr[i][c] = __builtin_bit_cast(
-          f32x4, __builtin_amdgcn_raw_buffer_load_b128(kres, 4 * (at[i] + min(c, d / 4 - 1) * step[i]), 0, 0));
+          f32x4, __builtin_amdgcn_raw_buffer_load_b128(kres, (int)(at[i] + 4u * (uint32_t)(min(c, d / 4 - 1) * step[i])), 0, 0));
 #pragma unroll
     for (int i = 0; i < NH; ++i)
 #pragma unroll
       for (int c = 0; c < DP / 4; ++c)
         vr[i][c] = __builtin_bit_cast(
-            f32x4, __builtin_amdgcn_raw_buffer_load_b128(vres, 4 * (at[i] + min(c, d / 4 - 1) * step[i]), 0, 0));
+            f32x4,
+            __builtin_amdgcn_raw_buffer_load_b128(vres, (int)(at[i] + 4u * (uint32_t)(min(c, d / 4 - 1) * step[i])), 0, 0));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {

@@ -6,6 +6,7 @@ Tolerances (max|err| / max|ref|): 1e-5 for fp32 inputs, 1e-2 for bf16 inputs,
 import numpy as np
 import pytest
 
+import synth
 from gpu_helpers import DCP_BF16, DCP_F32, Device, log, rel_err, sample_rows, workload
 
 pytestmark = pytest.mark.gpu
@@ -86,6 +87,30 @@ def test_general_path_shapes(torch_cuda, n_tok, c_s, c_z, h, d, dtype, n_kb):
         sub = rows[(rows >= 3) & (rows < n_tok - 2)]
         out = _np(dv.attention(3, n_tok - 5, n_kb, out_dtype=DCP_BF16))[sub - 3]
         assert rel_err(out, ref[np.isin(rows, sub)]) <= TOL_BF16
+
+
+@pytest.mark.parametrize("n_tok,n_kb,c_z,h,d", [(40, 1, 32, 4, 32), (131, 3, 128, 8, 16), (300, 1, 64, 16, 8),
+                                                (601, 1, 32, 4, 16), (33, 2, 24, 2, 6)])
+def test_general_path_infinite_value(torch_cuda, n_tok, n_kb, c_z, h, d):
+    """v of one output overflows to +inf at the last key (a part's last, off the 16-key tiles): that
+    output is +inf in every row, none is NaN, and the others are what they are without it."""
+    log(f"case general path, infinite v at key {n_tok - 1} of {n_tok}, n_kb={n_kb} c_z={c_z} H={h} d={d}")
+    wl = workload(n_tok=n_tok, c_s=64, c_z=c_z, n_heads=h, head_dim=d, dtype="f32")
+    s = synth.s_host(wl).copy()
+    s[:, 0] = 0.0
+    s[-1, 0] = 1e30
+    dv = Device(wl, affine=True, s_override=s)
+    for name in ("w_q", "w_k", "w_v", "w_g"):
+        dv.w_host[name] = dv.w_host[name].copy()
+        dv.w_host[name][:, 0] = 0.0
+    ref = dv.oracle_rows(np.arange(n_tok))
+    dv.w_host["w_v"][5, 0] = 1e30
+    for name in ("w_q", "w_k", "w_v", "w_g"):
+        dv.w[name] = torch_cuda.from_numpy(np.ascontiguousarray(dv.w_host[name])).to(dv.dev)
+    got = _np(dv.attention(0, n_tok, n_kb))
+    assert np.all(got[:, 5] == np.inf)
+    rest = np.arange(h * d) != 5
+    assert rel_err(got[:, rest], ref[:, rest]) <= TOL_F32
 
 
 # ----------------------------------------------------------------------------- fused bf16 path
