@@ -27,7 +27,7 @@
 //                      every 1 KB LDS read also costs matrix-core issue time,
 //                      which is why each weight fragment serves two pair tiles.
 //   trans_split_kernel small pair counts: the waves of a workgroup share 32
-//                      pairs and split the hidden units.
+//                      pairs and split the hidden units, then the output tiles.
 // The fp32 path is in transition_f32.hip.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -323,24 +323,31 @@ __global__ void __launch_bounds__(64 * kWaves) trans_kernel(TransArgs a) {
 // ----------------------------------------------------------------------------- few pairs
 // trans_kernel's time for one group is the chain of its 8 weight chunks through
 // LDS, about 23 us however few pairs there are, and 256 pairs per workgroup
-// leave most CUs idle. Here the waves of a workgroup share 32 pairs and split
-// the hidden units: wave w takes pairs of hidden tiles 2w and 2w + 1 (64
-// units), reads their weights straight from L2 (each 1 KB fragment once per
-// workgroup, 24 in flight) and the eight partial outputs are added in wave
-// order through LDS. Bound by the latency of those loads and of the two
-// exchanges: 2000 pairs 25.8 -> 11.7 us, 8192 pairs 26.0 -> 12.0 (the whole
-// call, weight preparation included).
+// leave most CUs idle. Here the waves of a workgroup share 32 pairs. Wave w first
+// takes pairs of hidden tiles 2w and 2w + 1 (64 units) to h', which the waves
+// exchange through LDS (32 KB), then output tile w over all 512 units. Weights
+// come straight from L2, each 1 KB fragment once per workgroup. Every product
+// and sum is trans_kernel's, in its order, from z on: a pair has the same bits
+// in a call of any size. Bound by the latency of the loads and of the exchange:
+// 2000 pairs 13.0 us, 8192 13.3, 26.1 and 26.5 with trans_kernel (the whole call,
+// weight preparation included). Eight partial outputs added at the end, without
+// the exchange, take as long (13.5, 13.5; 16384 pairs 21.2 against 22.1) but round
+// otherwise than trans_kernel.
 constexpr int kSplitPairs = 32;
-// Up to two rounds of workgroups over the 256 CUs: 16384 pairs take 19.7 us
-// against 26.0 with trans_kernel, a third round 27.7 against 26.1.
+// Up to two rounds of workgroups over the 256 CUs: 16384 pairs take 22.1 us
+// against 26.8 with trans_kernel, and a round adds 9 (24576 pairs: 27.2 with
+// trans_kernel).
 constexpr int64_t kSplitMax = 2 * 256 * kSplitPairs;
 constexpr int kSplitTiles = kHt / 2 / kWaves;  // pairs of hidden tiles per wave
+static_assert(kWaves == kCz / 16, "one output tile per wave");
 __global__ void __launch_bounds__(64 * kWaves) trans_split_kernel(TransArgs a) {
-  __shared__ __attribute__((aligned(16))) f32x4 s_part[kWaves][16][64];  // 128 KB: [wave][ct, pair tile][lane]
+  __shared__ __attribute__((aligned(16))) u32x4 s_h[kHt / 2][2][64];  // 32 KB: [pair of hidden tiles][pair tile][lane]
+  __shared__ __attribute__((aligned(16))) u32x4 s_o[kSplitPairs][16];     // 8 KB: the output
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t pair0 = (int64_t)blockIdx.x * kSplitPairs;
   const uint16_t* z_in = static_cast<const uint16_t*>(a.z_in);
+  const int c0 = out_channel(wave, 4 * g);  // lane (n, g) holds channels c0 .. c0 + 3 of the wave's output tile
   u32x4 zz[2][4];
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
@@ -348,16 +355,25 @@ __global__ void __launch_bounds__(64 * kWaves) trans_split_kernel(TransArgs a) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) zz[p][ks] = *reinterpret_cast<const u32x4*>(z_in + pr * kCz + 32 * ks + 8 * g);
   }
-  const char* wp = static_cast<const char*>(a.w_prep) + wave * kSplitTiles * kPairBytes + lane * 16;
-  // fragment r of a pair of hidden tiles, in the order of trans_kernel
+  const char* wp = static_cast<const char*>(a.w_prep) + lane * 16;
+  // W1' and W2 fragment r of this wave's q-th pair of hidden tiles, in the order of trans_kernel
   auto frag = [&](int q, int r) {
-    const int off = r < 16 ? (r >> 3) * 8192 + (r & 1) * 4096 + ((r >> 1) & 3) * 1024 : 16384 + (r - 16) * 1024;
-    return *reinterpret_cast<const u32x4*>(wp + q * kPairBytes + off);
+    return *reinterpret_cast<const u32x4*>(wp + (wave * kSplitTiles + q) * kPairBytes + (r >> 3) * 8192 +
+                                           (r & 1) * 4096 + ((r >> 1) & 3) * 1024);
   };
-  u32x4 wf[24];
+  u32x4 wf[16], w3[kHt / 2];  // w3: this wave's output tile over every pair of hidden tiles
 #pragma unroll
-  for (int r = 0; r < 24; ++r) wf[r] = frag(0, r);
+  for (int r = 0; r < 16; ++r) wf[r] = frag(0, r);
   __builtin_amdgcn_sched_barrier(0);
+
+  u32x2 zc[2];  // z of the wave's output tile: chunk wave / 2, half wave % 2
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    u32x4 c = zz[p][0];
+#pragma unroll
+    for (int ks = 1; ks < 4; ++ks) c = wave >> 1 == ks ? zz[p][ks] : c;
+    zc[p] = wave & 1 ? u32x2{c[2], c[3]} : u32x2{c[0], c[1]};
+  }
 
   // LayerNorm, by every wave for all 32 pairs (its own operands, no exchange)
   bf16x8 nv[2][4];
@@ -398,64 +414,57 @@ __global__ void __launch_bounds__(64 * kWaves) trans_split_kernel(TransArgs a) {
   }
 
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[8][2], h[2][2][2];
+  f32x4 h[2][2][2];
 #pragma unroll
-  for (int ct = 0; ct < 8; ++ct) acc[ct][0] = acc[ct][1] = zero;
-  bf16x8 hv[2];
+  for (int q = 0; q < kSplitTiles; ++q) {
 #pragma unroll
-  for (int q = 0; q < kSplitTiles; ++q)
-#pragma unroll
-    for (int r = 0; r < 24; ++r) {
+    for (int r = 0; r < 16; ++r) {
       const bf16x8 w = as_bf16x8(wf[r]);
-      if (q + 1 < kSplitTiles) wf[r] = frag(q + 1, r);
-      if (r < 16) {
-        const int tt = r >> 3, ks = (r >> 1) & 3, m = r & 1;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) h[m][tt][p] = mfma32(w, nv[p][ks], ks == 0 ? zero : h[m][tt][p]);
-      } else {
-        if (r == 16)  // h' as the B operand over the 32 units, as in trans_kernel
-#pragma unroll
-          for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const float x = h[0][j >> 2][p][j & 3];
-              hv[p][j] = (__bf16)(x * h[1][j >> 2][p][j & 3] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x)));
-            }
-#pragma unroll
-        for (int p = 0; p < 2; ++p) acc[r - 16][p] = mfma32(w, hv[p], acc[r - 16][p]);
+      if (q + 1 < kSplitTiles) {
+        wf[r] = frag(q + 1, r);
+        w3[r] = *reinterpret_cast<const u32x4*>(wp + r * kPairBytes + 16384 + wave * 1024);
       }
-      __builtin_amdgcn_sched_barrier(0);  // the next tiles' loads stay where they are
+      const int tt = r >> 3, ks = (r >> 1) & 3, m = r & 1;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) h[m][tt][p] = mfma32(w, nv[p][ks], ks == 0 ? zero : h[m][tt][p]);
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay where they are
     }
+    // h' as the B operand over the 32 units, as in trans_kernel
 #pragma unroll
-  for (int ct = 0; ct < 8; ++ct)
+    for (int p = 0; p < 2; ++p) {
+      bf16x8 hv;
 #pragma unroll
-    for (int p = 0; p < 2; ++p) s_part[wave][2 * ct + p][lane] = acc[ct][p];
-  __syncthreads();
-
-  // wave w adds and stores channels 32 (w % 4) .. +31 of pair tile w / 4: lane
-  // (n, g) the 16 bytes of channels 32 ks + 8g .. +7. Every wave has read z
-  // before the barrier, so z_out may be z_in.
-  const int ks = wave & 3, p = wave >> 2;
-  const int64_t pr = pair0 + 16 * p + n;
-  if (pr >= a.n_pairs) return;
-  const u32x4 zr = *reinterpret_cast<const u32x4*>(z_in + pr * kCz + 32 * ks + 8 * g);
-  bf16x8 o;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    f32x4 sum;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t w = zr[2 * s + (i >> 1)];
-      sum[i] = __uint_as_float((i & 1) ? (w & 0xFFFF0000u) : (w << 16));
+      for (int j = 0; j < 8; ++j) {
+        const float x = h[0][j >> 2][p][j & 3];
+        hv[j] = (__bf16)(x * h[1][j >> 2][p][j & 3] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x)));
+      }
+      s_h[wave * kSplitTiles + q][p][lane] = __builtin_bit_cast(u32x4, hv);
     }
-    f32x4 part = s_part[0][2 * (2 * ks + s) + p][lane];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) part += s_part[w][2 * (2 * ks + s) + p][lane];
-    sum += part;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[4 * s + i] = (__bf16)sum[i];
   }
-  *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.z_out) + pr * kCz + 32 * ks + 8 * g) = __builtin_bit_cast(u32x4, o);
+  __syncthreads();
+  // Output tile `wave`. Every wave has read z before the barrier, so z_out may be z_in.
+  f32x4 acc[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+    acc[p] = f32x4{__uint_as_float(zc[p][0] << 16), __uint_as_float(zc[p][0] & 0xFFFF0000u),
+                   __uint_as_float(zc[p][1] << 16), __uint_as_float(zc[p][1] & 0xFFFF0000u)};
+#pragma unroll
+  for (int hp = 0; hp < kHt / 2; ++hp)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) acc[p] = mfma32(as_bf16x8(w3[hp]), as_bf16x8(s_h[hp][p][lane]), acc[p]);
+  // through LDS (16-byte chunks of a pair XOR its number) to stores of whole lines
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = (__bf16)acc[p][i];
+    reinterpret_cast<u32x2*>(&s_o[16 * p + n][(c0 / 8) ^ n])[c0 / 4 & 1] = __builtin_bit_cast(u32x2, o);
+  }
+  __syncthreads();
+  const int row = threadIdx.x >> 4, chunk = threadIdx.x & 15;
+  if (pair0 + row < a.n_pairs)
+    *(reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.z_out) + (pair0 + row) * kCz) + chunk) =
+        s_o[row][chunk ^ (row & 15)];
 }
 
 }  // namespace

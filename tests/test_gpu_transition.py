@@ -110,6 +110,22 @@ def test_bf16_split_kernel_edges(n):
     assert torch.equal(zc[n:], zt[n:])
 
 
+@pytest.mark.parametrize("n", [1, 31, 1000, 8192, 16384])
+def test_bf16_chunks_match_the_whole_call(n):
+    """Pairs have the same bits whichever kernel the size of the call chooses: a tensor processed in
+    chunks is the tensor processed at once, in place or not."""
+    import torch
+    wl, hidden = synth.transition_workload("trans192_bf16")
+    w = synth.transition_weights(wl, hidden, affine=True)
+    zt = dev(synth.z_host(wl, range(192)).reshape(-1, 128))
+    whole = run(zt, w, DCP_BF16)
+    for r in sorted({0, 7 * n, len(zt) - n} & set(range(len(zt) - n + 1))):
+        part = zt[r:r + n].clone()
+        assert torch.equal(run(part, w, DCP_BF16, n_pairs=n), whole[r:r + n])
+        run(part, w, DCP_BF16, n_pairs=n, in_place=True)
+        assert torch.equal(part, whole[r:r + n])
+
+
 def test_bf16_full_size_in_place_sampled():
     """The 24000-token pair tensor (147 GB, bf16) updated in place in one call,
     as the benchmark does; sampled pairs against the oracle on the generator's
