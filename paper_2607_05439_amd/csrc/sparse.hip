@@ -498,11 +498,14 @@ sparse_attn_kernel(SparseAttnArgs a) {
     }
   };
   // ... then the online softmax (integer maxima, exact power-of-two
-  // rescaling) and the weighted V
-  auto weigh = [&](int buf, const float (&lg)[kUnroll]) {
+  // rescaling) and the weighted V, kSub rows of a lane at a time: an fp32 weight
+  // depends on the maximum so far (the subtraction rounds), so its steps are the
+  // same whatever the batch, and a query's bits whatever the call's size
+  constexpr int kSub = kBf16 ? kUnroll : 2;
+  auto weigh = [&](int buf, int u0, const float (&lg)[kUnroll]) {
     float mx = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) mx = vmax(mx, lg[u]);
+    for (int u = u0; u < u0 + kSub; ++u) mx = vmax(mx, lg[u]);
     mx = across_max<NPI>(mx);
     const float m_new = fmaxf(m_run, ceilf(mx));
     if (m_new != m_run) {  // lane-varying (per head); only a rescale of the state
@@ -514,7 +517,7 @@ sparse_attn_kernel(SparseAttnArgs a) {
     }
     const float m_use = m_run == -INFINITY ? 0.0f : m_run;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
+    for (int u = u0; u < u0 + kSub; ++u) {
       const float p = __builtin_amdgcn_exp2f(lg[u] - m_use);
       if constexpr (kBf16) {
         // the weight as bf16 pairs (p, 0) and (0, p): one dot2 per element (no
@@ -678,7 +681,8 @@ sparse_attn_kernel(SparseAttnArgs a) {
       float lg[kUnroll];
       logits(0, b0, lg);
       issue_k(0, off);
-      weigh(0, lg);
+#pragma unroll
+      for (int u0 = 0; u0 < kUnroll; u0 += kSub) weigh(0, u0, lg);
       issue_v(0, off);
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) prev[u] = off[u];

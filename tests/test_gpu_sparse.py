@@ -164,9 +164,8 @@ def test_f32_gathered_and_k256():
 @pytest.mark.parametrize("dtype,k", [("bf16", 100), ("bf16", 200), ("f32", 100), ("f32", 200)])
 def test_few_atoms_and_few_queries(dtype, k):
     """Both sides of the rules for few atoms (8192) and few queries (2048), and
-    ragged ends of their 64-atom groups: bf16 rows are the same bits whichever
-    kernels serve them; fp32 batches differ in the order of their running maxima, so
-    those rows agree to a few fp32 roundings of sums of k terms (2e-6)."""
+    ragged ends of their 64-atom groups: rows are the same bits whichever
+    kernels serve them."""
     import torch
     import paper_2607_05439_amd as dcp
     code, dt = (DCP_BF16, torch.bfloat16) if dtype == "bf16" else (DCP_F32, torch.float32)
@@ -190,7 +189,4 @@ def test_few_atoms_and_few_queries(dtype, k):
         ref = call(n_max, q_max, nbr)
         for rows in (q_max, 2048, 65):
             got = call(n, rows, nbr)
-            if dtype == "bf16":
-                assert torch.equal(got, ref[:rows])
-            else:
-                assert ((got - ref[:rows]).norm() / ref[:rows].norm()).item() <= 2e-6
+            assert torch.equal(got, ref[:rows])
