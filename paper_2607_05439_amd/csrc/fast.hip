@@ -451,7 +451,7 @@ __global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
     const int h = kHw * wave + j;
     const float l = o[j][1][0];  // valid in lane group 2 (e = 24)
     if (g == 2) {
-      const bool empty = !(l > 0.0f);
+      const bool empty = l == 0.0f;  // (a NaN goes on to the merge)
       a.m_parts[((int64_t)part * kH + h) * a.n_q + row] = empty ? -INFINITY : m[j] - kShift;
       a.l_parts[((int64_t)part * kH + h) * a.n_q + row] = empty ? 0.0f : l;
     }

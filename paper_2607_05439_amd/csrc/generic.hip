@@ -245,13 +245,12 @@ __global__ void __launch_bounds__(64) gen_attn_any_kernel(GenAttnArgs a) {
     float mx = -INFINITY;
     for (int t = 0; t < 64; ++t) mx = fmaxf(mx, st_m[t][h]);
     float l = 0.0f, acc = 0.0f;
-    if (mx != -INFINITY)
-      for (int t = 0; t < 64; ++t) {
-        if (st_m[t][h] == -INFINITY) continue;
-        const float sc = expf(st_m[t][h] - mx);
-        l = fmaf(sc, st_l[t][h], l);
-        acc = fmaf(sc, st_acc[t][x], acc);
-      }
+    for (int t = 0; t < 64; ++t) {
+      if (st_m[t][h] == -INFINITY && st_l[t][h] == 0.0f) continue;
+      const float sc = expf(st_m[t][h] - mx);
+      l = fmaf(sc, st_l[t][h], l);
+      acc = fmaf(sc, st_acc[t][x], acc);
+    }
     a.acc_parts[((int64_t)part * a.n_q + row) * hd + x] = acc;
     if (x % d == 0) {
       a.m_parts[((int64_t)part * H + h) * a.n_q + row] = mx;

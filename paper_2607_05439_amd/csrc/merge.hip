@@ -2,6 +2,8 @@
 // steps: Appendix "Q/K/V layout and the ring loop"), then out = gate*acc/l.
 // One thread per (row, h*d + e), or per four (two, on small layers) channels
 // of one head when the head size allows; parts are folded in increasing order.
+// A part without keys (m = -inf, l = 0) is left out. One whose logits are all
+// NaN also has m = -inf, but l = NaN, which goes into the result as any NaN does.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -21,15 +23,14 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
     float mx = -INFINITY;
     for (int p = 0; p < a.n_parts; ++p) mx = fmaxf(mx, a.m[((int64_t)p * a.n_heads + h) * a.n_rows + r]);
     float l = 0.0f, acc = 0.0f;
-    if (mx != -INFINITY) {
-      for (int p = 0; p < a.n_parts; ++p) {
-        const float mp = a.m[((int64_t)p * a.n_heads + h) * a.n_rows + r];
-        if (mp == -INFINITY) continue;
-        // base-2 partials have integer maxima: the factor is an exact power of two
-        const float sc = a.log2_units ? ldexpf(1.0f, (int)(mp - mx)) : expf(mp - mx);
-        l = fmaf(sc, a.l[((int64_t)p * a.n_heads + h) * a.n_rows + r], l);
-        acc = fmaf(sc, a.acc[((int64_t)p * a.n_rows + r) * hd + x], acc);
-      }
+    for (int p = 0; p < a.n_parts; ++p) {
+      const float mp = a.m[((int64_t)p * a.n_heads + h) * a.n_rows + r];
+      const float lp = a.l[((int64_t)p * a.n_heads + h) * a.n_rows + r];
+      if (mp == -INFINITY && lp == 0.0f) continue;
+      // base-2 partials have integer maxima: the factor is an exact power of two
+      const float sc = a.log2_units ? ldexpf(1.0f, (int)(mp - mx)) : expf(mp - mx);
+      l = fmaf(sc, lp, l);
+      acc = fmaf(sc, a.acc[((int64_t)p * a.n_rows + r) * hd + x], acc);
     }
     if (a.acc_out) a.acc_out[t] = acc;
     if (x % a.head_dim == 0) {
@@ -40,7 +41,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeArgs a) {
     }
     if (a.out) {
       const float gt = a.gate ? a.gate[t] : 1.0f;
-      const float o = l > 0.0f ? gt * (acc / l) : 0.0f;
+      const float o = l == 0.0f ? 0.0f : gt * (acc / l);
       if (a.out_bf16)
         static_cast<__bf16*>(a.out)[t] = (__bf16)o;
       else
@@ -87,27 +88,25 @@ __device__ __forceinline__ void merge_vec(const MergeArgs& a) {
     float acc[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.0f;
-    if (mx != -INFINITY) {
-      const float* ap = a.acc + (size_t)r * hd + (size_t)V * xv;
-      // four parts' loads at a time (a part past the end repeats the last
-      // one and is skipped), folded in increasing order
-      for (int p0 = 0; p0 < a.n_parts; p0 += 4) {
-        float mv[4], lv[4], vv[4][V];
+    const float* ap = a.acc + (size_t)r * hd + (size_t)V * xv;
+    // four parts' loads at a time (a part past the end repeats the last
+    // one and is skipped), folded in increasing order
+    for (int p0 = 0; p0 < a.n_parts; p0 += 4) {
+      float mv[4], lv[4], vv[4][V];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int p = min(p0 + j, a.n_parts - 1);
-          mv[j] = m[p * pm];
-          lv[j] = l_in[p * pm];
-          load_vec<V>(ap + p * part, vv[j]);
-        }
+      for (int j = 0; j < 4; ++j) {
+        const int p = min(p0 + j, a.n_parts - 1);
+        mv[j] = m[p * pm];
+        lv[j] = l_in[p * pm];
+        load_vec<V>(ap + p * part, vv[j]);
+      }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (p0 + j >= a.n_parts || mv[j] == -INFINITY) continue;
-          const float sc = a.log2_units ? ldexpf(1.0f, (int)(mv[j] - mx)) : expf(mv[j] - mx);
-          l = fmaf(sc, lv[j], l);
+      for (int j = 0; j < 4; ++j) {
+        if (p0 + j >= a.n_parts || (mv[j] == -INFINITY && lv[j] == 0.0f)) continue;
+        const float sc = a.log2_units ? ldexpf(1.0f, (int)(mv[j] - mx)) : expf(mv[j] - mx);
+        l = fmaf(sc, lv[j], l);
 #pragma unroll
-          for (int i = 0; i < V; ++i) acc[i] = fmaf(sc, vv[j][i], acc[i]);
-        }
+        for (int i = 0; i < V; ++i) acc[i] = fmaf(sc, vv[j][i], acc[i]);
       }
     }
     const size_t e0 = (size_t)t * V;  // = r * hd + V * xv
@@ -118,7 +117,7 @@ __device__ __forceinline__ void merge_vec(const MergeArgs& a) {
       if (a.l_out) a.l_out[(size_t)h * nr + r] = l;
     }
     if (a.out) {
-      const bool any = l > 0.0f;
+      const bool any = l != 0.0f;
       float gt[V], o[V];
       if (a.gate)
         load_vec<V>(a.gate + e0, gt);

@@ -260,3 +260,43 @@ def test_part_partition_edges(torch_cuda, n_tok, q_row0, n_q, n_kb):
     assert rel_err(got, d.oracle_rows(np.arange(q_row0, q_row0 + n_q))) <= TOL_BF16
     assert rel_err(_np(d.attention(q_row0, n_q, 1)), got) <= TOL_BLOCKED
     assert np.array_equal(_np(d.attention(q_row0, n_q, n_kb)), got)
+
+
+@pytest.mark.parametrize("n_tok,c_z,h,d,dtype,q_row0,n_q,n_kb", [
+    (100, 128, 16, 24, "bf16", 0, 100, 1), (100, 128, 16, 24, "bf16", 40, 20, 3), (1400, 128, 16, 24, "bf16", 500, 200, 1),
+    (40, 32, 4, 32, "f32", 0, 40, 1), (70, 128, 8, 16, "f32", 0, 70, 3), (300, 32, 4, 16, "f32", 0, 300, 2),
+    (70, 24, 2, 6, "f32", 0, 70, 1), (70, 24, 2, 6, "f32", 0, 70, 4)])
+def test_nan_of_an_unmasked_pair_or_token_propagates(torch_cuda, n_tok, c_z, h, d, dtype, q_row0, n_q, n_kb):
+    """A NaN in one pair vector makes its row NaN and no other; one in the s of a key makes every row
+    that attends to it NaN; in a call and in partial states merged, whichever part the key lies in."""
+    import paper_2607_05439_amd as dcp
+    log(f"case NaN: N={n_tok} c_z={c_z} H={h} d={d} {dtype} rows {q_row0}+{n_q} n_kb={n_kb}")
+    wl = workload(n_tok=n_tok, c_s=64, c_z=c_z, n_heads=h, head_dim=d, dtype=dtype)
+    m = np.ones(n_tok, np.uint8)
+    m[2::5] = 0
+    dv = Device(wl, mask=m)
+    key, row = n_tok - 1 - (m[-1] == 0), n_q // 2
+    clean = dv.attention(q_row0, n_q, n_kb)
+
+    def states_merged():
+        shape, f32 = dv.shape(), dict(dtype=torch_cuda.float32, device="cuda:0")
+        ms, ls = (torch_cuda.empty((2, h, n_q), **f32) for _ in range(2))
+        acc, gate = torch_cuda.empty((2, n_q, h * d), **f32), torch_cuda.empty((n_q, h * d), **f32)
+        ws = torch_cuda.empty(dcp.dcp_workspace_size(shape, n_q, 1), dtype=torch_cuda.uint8, device="cuda:0")
+        cut, z_ptr = n_tok - 4, dv.z.data_ptr() + q_row0 * n_tok * c_z * dv.z.element_size()
+        for i, (k0, k1) in enumerate(((0, cut), (cut, n_tok))):
+            dcp.dcp_pair_bias_attention_partial(shape, dv.weights(), dv.s, z_ptr, dv.mask, q_row0, n_q, k0, k1, ms[i],
+                                                ls[i], acc[i], gate, ws, ws.numel())
+        out = torch_cuda.empty((n_q, h * d), **f32)
+        dcp.dcp_block_merge(2, n_q, h, d, ms, ls, acc, None, None, None, gate, out, DCP_F32)
+        return out
+
+    merged = states_merged()
+    dv.z[q_row0 + row, key, 3] = float("nan")
+    for got, ref in ((dv.attention(q_row0, n_q, n_kb), clean), (states_merged(), merged)):
+        assert got[row].isnan().all()
+        others = np.arange(n_q) != row
+        assert torch_cuda.equal(got[others], ref[others])
+    dv.s[key, 1] = float("nan")
+    assert dv.attention(q_row0, n_q, n_kb).isnan().all()
+    assert states_merged().isnan().all()
