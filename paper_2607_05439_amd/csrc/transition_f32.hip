@@ -94,12 +94,19 @@ __global__ void __launch_bounds__(256, CT > 8 ? 1 : 2) trans_f32_kernel(TransGen
   // is what the registers hold at two waves per SIMD.
   constexpr int kHalf = CT / 2;
   f32x4 w1[CT], w2[CT], w3[CT];
+  // Channels past c_z of W1 and W2 are read out of range, zeros: z is 0 there, and 0
+  // times the row's last chunk would make a NaN of an infinite weight.
+  const __amdgpu_buffer_rsrc_t res1 =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w1), 0, a.hidden * a.c_z * 4, kRawBufferFlags);
+  const __amdgpu_buffer_rsrc_t res2 =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.w2), 0, a.hidden * a.c_z * 4, kRawBufferFlags);
   auto load12 = [&](int ht, int j0) {
-    const int64_t r = (int64_t)(16 * ht + n) * a.c_z;
+    const int row = 16 * ht * a.c_z * 4;
 #pragma unroll
     for (int j = j0; j < j0 + kHalf; ++j) {
-      w1[j] = chunk(a.w1 + r + ch[j]);
-      w2[j] = chunk(a.w2 + r + ch[j]);
+      const int off = inside(j) ? (n * a.c_z + 16 * j + 4 * g) * 4 : kOutOfRange;
+      w1[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(res1, off, row, 0));
+      w2[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(res2, off, row, 0));
     }
   };
   auto load3 = [&](int ht, int j0) {

@@ -181,3 +181,18 @@ def test_f32_widths_and_tile_edges(c_z, hidden):
     dcp.dcp_pair_transition(n, c_z, hidden, DCP_F32, 1e-5, off[1:], W["w2"], W["w3"], W["gamma"], W["beta"], zt, out,
                             None, 0)
     assert rel_err(host_f64(out), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("c_z,hidden", [(20, 48), (32, 128), (100, 400), (132, 16)])
+@pytest.mark.parametrize("name", ["w1", "w2"])
+def test_f32_infinite_weight(c_z, hidden, name):
+    """An infinite weight of W1 or W2 in the last channel: the outputs it reaches are infinite (the
+    products with the finite others are not 0), none is NaN."""
+    rng = np.random.default_rng(c_z)
+    w = {"w1": 0.1 + 0.2 * rng.random((hidden, c_z)), "w2": 0.1 + 0.2 * rng.random((hidden, c_z)),
+         "w3": 0.1 + 0.2 * rng.random((c_z, hidden)), "gamma": np.full(c_z, 0.1), "beta": np.ones(c_z)}
+    w = {k: v.astype(np.float32) for k, v in w.items()}  # LN z = 1 + 0.1 (..) > 0: every product is positive
+    w[name][hidden - 1, c_z - 1] = np.inf
+    z = rng.uniform(-1, 1, (40, c_z)).astype(np.float32)
+    got = host_f64(run(dev(z), w, DCP_F32))
+    assert np.all(got == np.inf)
