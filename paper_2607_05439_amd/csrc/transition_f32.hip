@@ -29,11 +29,14 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // The four waves share the pairs and take every fourth tile of 16 hidden units,
 // each streaming its own weight tiles from L2 one tile ahead; their partial sums
 // meet in LDS and are added in wave order. Splitting the hidden units rather
-// than the pairs keeps four waves busy on each 16 pairs. What bounds it: the
-// matrix cores are busy 42% of the time on 36864 pairs of 128 channels; without
-// the weight loads (a timing probe) one tile per workgroup takes 145 us instead
-// of 236, two 169 instead of 196, so two tiles are limited by the uneven last
-// round of workgroups, one by the latency of the weights. The SiLU costs 3 us.
+// than the pairs keeps four waves busy on each 16 pairs. What bounds it: 36864
+// pairs of 128 channels take 165 us with two tiles per workgroup and 233 with
+// one, where the products alone need 95 at the rate of a large fp32 matrix
+// product; without the weight loads in the loop (a timing probe) 149 and 134. So
+// one tile is limited by the latency of the weights, two by the uneven last round
+// of workgroups (1152 of them, two per CU, are 2.25 rounds). gamma and beta are
+// read once for both tiles: a tile at a time they and the addresses did not fit
+// the registers (24 spilled, 185 us).
 template <int CT, int P>
 __global__ void __launch_bounds__(256, CT > 8 ? 1 : 2) trans_f32_kernel(TransGenArgs a) {
   __shared__ f32x4 red[4][P][CT][64];
@@ -58,6 +61,7 @@ __global__ void __launch_bounds__(256, CT > 8 ? 1 : 2) trans_f32_kernel(TransGen
 #pragma unroll
     for (int j = 0; j < CT; ++j) nz[p][j] = chunk(z + ch[j]);
   }
+  float rstd[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     float s = 0.0f, v = 0.0f;
@@ -73,14 +77,16 @@ __global__ void __launch_bounds__(256, CT > 8 ? 1 : 2) trans_f32_kernel(TransGen
         nz[p][j][i] = inside(j) ? nz[p][j][i] - mu : 0.0f;
         v = fmaf(nz[p][j][i], nz[p][j][i], v);
       }
-    const float rstd = 1.0f / sqrtf(sum4(v) / (float)a.c_z + a.eps);
+    rstd[p] = 1.0f / sqrtf(sum4(v) / (float)a.c_z + a.eps);
+  }
 #pragma unroll
-    for (int j = 0; j < CT; ++j) {
-      const f32x4 ga = a.gamma ? chunk(a.gamma + ch[j]) : f32x4{1.f, 1.f, 1.f, 1.f};
-      const f32x4 be = a.beta ? chunk(a.beta + ch[j]) : zero;
+  for (int j = 0; j < CT; ++j) {
+    const f32x4 ga = a.gamma ? chunk(a.gamma + ch[j]) : f32x4{1.f, 1.f, 1.f, 1.f};
+    const f32x4 be = a.beta ? chunk(a.beta + ch[j]) : zero;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) nz[p][j][i] = inside(j) ? ga[i] * (nz[p][j][i] * rstd) + be[i] : 0.0f;
-    }
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nz[p][j][i] = inside(j) ? ga[i] * (nz[p][j][i] * rstd[p]) + be[i] : 0.0f;
   }
 
   f32x4 out[P][CT];
@@ -173,11 +179,12 @@ __global__ void __launch_bounds__(256, CT > 8 ? 1 : 2) trans_f32_kernel(TransGen
 }
 
 // Two tiles of 16 pairs per workgroup halve the weight traffic (and the stalls
-// on it) but also the workgroups: one tile per workgroup is faster up to three
-// workgroups per CU (9000 pairs of 128 channels: 82 us against 90 us; 64
-// channels 25.5 against 26.8), two beyond (16384 pairs: 89 against 113 us; 64
-// channels 28 against 34).
-constexpr int64_t kTransF32SmallPairs = 3 * 256 * 16;
+// on it) but also the workgroups: while one tile per workgroup leaves a CU no
+// second workgroup, one is faster (4096 pairs of 128 channels: 28.4 us against
+// 34.0; 64 channels 9.2 against 12.0), and two beyond (4097 pairs: 33.7 against
+// 49.8, 9000 71.5 against 78.5; 64 channels 12.1 against 15.1; 100 channels lose
+// 1 % between 9000 and 12288).
+constexpr int64_t kTransF32SmallPairs = 256 * 16;
 
 template <int CT, int P>
 hipError_t launch_trans_f32(const TransGenArgs& a, hipStream_t st) {
@@ -230,8 +237,7 @@ __global__ void __launch_bounds__(256) trans_gen_kernel(TransGenArgs a) {
 hipError_t launch_transition_gen(const TransGenArgs& a, hipStream_t st) {
   // The matrix-core kernel wherever its 16-byte loads fit; the vector kernel
   // takes any other width or alignment (192 x 192 pairs of 128 channels: 3450 us
-  // on the vector units, 196 us here, where the products alone need 94 us at the
-  // rate of a large fp32 matrix product).
+  // on the vector units, 165 us here).
   const auto at16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   if (a.c_z % 4 == 0 && a.hidden % 16 == 0 && at16(a.w1) && at16(a.w2) && at16(a.w3) && at16(a.gamma) && at16(a.beta)) {
     if (a.c_z > 128) return launch_trans_f32<16, 1>(a, st);

@@ -166,7 +166,7 @@ def test_f32_widths_and_tile_edges(c_z, hidden):
          "w3": rng.standard_normal((c_z, hidden)) / np.sqrt(hidden), "gamma": 1 + 0.25 * rng.standard_normal(c_z),
          "beta": 0.25 * rng.standard_normal(c_z)}
     w = {k: v.astype(np.float32) for k, v in w.items()}
-    for n in (1, 15, 17, 33) + ((12288, 12289) if c_z == 32 else ()):
+    for n in (1, 15, 17, 33) + ((4096, 4097, 12288, 12289) if c_z == 32 else ()):
         z = rng.standard_normal((n, c_z)).astype(np.float32)
         ref = oracle.transition(z, w["w1"], w["w2"], w["w3"], w["gamma"], w["beta"])
         zt = dev(z)
@@ -181,6 +181,20 @@ def test_f32_widths_and_tile_edges(c_z, hidden):
     dcp.dcp_pair_transition(n, c_z, hidden, DCP_F32, 1e-5, off[1:], W["w2"], W["w3"], W["gamma"], W["beta"], zt, out,
                             None, 0)
     assert rel_err(host_f64(out), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("c_z,hidden", [(32, 128), (100, 400), (128, 512), (256, 64)])
+def test_f32_chunks_match_the_whole_call(c_z, hidden):
+    """One tile of 16 pairs per workgroup or two, by the size of the call: the same bits."""
+    import torch
+    rng = np.random.default_rng(c_z)
+    w = {"w1": rng.standard_normal((hidden, c_z)), "w2": rng.standard_normal((hidden, c_z)),
+         "w3": rng.standard_normal((c_z, hidden)), "gamma": rng.standard_normal(c_z), "beta": rng.standard_normal(c_z)}
+    w = {k: v.astype(np.float32) for k, v in w.items()}
+    z = dev(rng.standard_normal((4200, c_z)).astype(np.float32))
+    whole = run(z, w, DCP_F32)
+    for r, n in ((0, 4096), (100, 4097), (4199, 1), (7, 1000)):
+        assert torch.equal(run(z[r:r + n].clone(), w, DCP_F32), whole[r:r + n])
 
 
 @pytest.mark.parametrize("c_z,hidden", [(20, 48), (32, 128), (100, 400), (132, 16)])
