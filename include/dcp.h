@@ -107,14 +107,18 @@ size_t dcp_workspace_bytes(const dcp_shape* shape, int64_t n_q, int32_t n_key_bl
  *               &z[q_row0, 0, 0] of a contiguous z[N, N, c_z]; 16-byte aligned
  *   key_mask    [N] uint8, 1 = attend, 0 = masked; NULL = every key attends
  *   n_q         0 <= n_q, q_row0 >= 0, q_row0 + n_q <= N (n_q = 0 is a no-op)
- *   n_key_blocks in [1, N]: keys are split into this many blocks by the
- *               paper's chunk rule (Appendix "Chunk distribution algorithm":
- *               block p has floor(N/P) + [p < N mod P] keys) and the blocks'
- *               partial states are merged in increasing order, as the ring
- *               steps of the paper's 2D scheme do. Any value gives the same
- *               result up to fp32 rounding order, which lets the library fold
- *               neighbouring blocks, or split one, into whatever partial
- *               states the chip runs fastest.
+ *   n_key_blocks in [1, N]: the key blocks of the paper's chunk rule (Appendix
+ *               "Chunk distribution algorithm": block p has floor(N/P) +
+ *               [p < N mod P] keys). Any value gives the same result up to fp32
+ *               rounding order. It sizes the workspace, and so bounds the number
+ *               of partial states; the partition of the keys is the library's
+ *               own: the fused path cuts whole 16-key tiles wherever that runs
+ *               fastest, the general path takes the blocks, or all keys in one.
+ *               It depends on N, n_q and n_key_blocks, so a row's last bits may
+ *               differ between calls over other stripes.
+ *               Partial states are merged in increasing key order, as the ring
+ *               steps of the paper's 2D scheme are. (For a partition of one's own
+ *               choice: dcp_pair_bias_attention_partial and dcp_block_merge.)
  *   out         [n_q, H*d] out_dtype, 16-byte aligned
  *   workspace   device scratch of at least dcp_workspace_size() bytes,
  *               256-byte aligned; contents on entry are ignored.

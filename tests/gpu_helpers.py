@@ -120,6 +120,51 @@ class Device:
                                 self.wl.head_dim, n_blocks=n_blocks)
 
 
+def ring_of_partials(d: "Device", q_row0: int, n_q: int, bounds: Sequence[int]):
+    """Partial states of the key ranges [bounds[i], bounds[i + 1]) merged in increasing order: the
+    same rows as one call, over a partition of the caller's choice. Returns a device tensor."""
+    import paper_2607_05439_amd as dcp
+    torch, wl, p = d.torch, d.wl, len(bounds) - 1
+    hd = wl.n_heads * wl.head_dim
+    f32 = dict(dtype=torch.float32, device=d.dev)
+    m, l = torch.empty((p, wl.n_heads, n_q), **f32), torch.empty((p, wl.n_heads, n_q), **f32)
+    acc, gate, out = torch.empty((p, n_q, hd), **f32), torch.empty((n_q, hd), **f32), torch.empty((n_q, hd), **f32)
+    shape = d.shape(DCP_F32)
+    ws = torch.empty(max(dcp.dcp_workspace_size(shape, n_q, 1), 256), dtype=torch.uint8, device=d.dev)
+    z_ptr = d.z.data_ptr() + q_row0 * wl.n_tok * wl.c_z * d.z.element_size()
+    for i in range(p):
+        dcp.dcp_pair_bias_attention_partial(shape, d.weights(), d.s, z_ptr, d.mask, q_row0, n_q, bounds[i],
+                                            bounds[i + 1], m[i], l[i], acc[i], gate if i == 0 else None, ws, ws.numel())
+    dcp.dcp_block_merge(p, n_q, wl.n_heads, wl.head_dim, m, l, acc, None, None, None, gate, out, DCP_F32)
+    return out
+
+
+def check_partitions(d: "Device", q_row0: int, n_q: int, whole, n_kb: int = 64, tol: float = 1e-6,
+                     tol_states: float = 1e-5) -> None:
+    """The rows of one fp32-output call (`whole`, n_q rows from q_row0) over other partitions of the
+    keys. n_key_blocks does not choose the partition, the library does, from the whole call's size:
+    so (1) stripes of few of the rows, which are split into more parts (other bits show that they
+    were), to `tol`, and (2) key ranges that meet inside 16-key tiles, where no partition of the
+    library's has an edge, to `tol_states` (their exported states are rounded to natural-log units)."""
+    torch, n = d.torch, d.wl.n_tok
+    den = max(whole.abs().max().item(), 1e-30)
+    rows = min(16, max(1, n_q // 2))
+    other_bits = False
+    for r in sorted({0, (n_q - rows) // 2, n_q - rows}):
+        part = d.attention(q_row0 + r, rows, min(n_kb, n))
+        err = (part - whole[r:r + rows]).abs().max().item() / den
+        log(f"  rows {r}+{rows} alone against {n_q} at once: rel diff {err:.3e}")
+        assert err <= tol
+        other_bits = other_bits or not torch.equal(part, whole[r:r + rows])
+    assert other_bits, "the stripes were split like the whole call"
+    inside = [b + (b % 16 == 0) for b in (5, n // 3, n // 2, n - 7) if 16 < n and 0 < b < n - 1]
+    bounds = [0, *sorted(set(inside)), n]
+    assert len(bounds) > 3 and all(b % 16 for b in bounds[1:-1])
+    err = (ring_of_partials(d, q_row0, n_q, bounds) - whole).abs().max().item() / den
+    log(f"  key ranges {bounds}: rel diff {err:.3e}")
+    assert err <= tol_states
+
+
 def sample_rows(n_tok: int, stripes, n_kb: int, n_random: int, mask: Optional[np.ndarray], seed: int = 0):
     """Rows the oracle checks at full size: the first and last row of every
     stripe and key block, some masked (padding) rows, and random rows."""

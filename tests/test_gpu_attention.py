@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_helpers import DCP_BF16, DCP_F32, Device, log, rel_err, sample_rows, workload
+from gpu_helpers import DCP_BF16, DCP_F32, Device, check_partitions, log, rel_err, sample_rows, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -83,6 +83,9 @@ def test_general_path_shapes(torch_cuda, n_tok, c_s, c_z, h, d, dtype, n_kb):
     assert rel_err(got, ref) <= TOL_F32
     assert rel_err(_np(dv.attention(0, n_tok, 1))[rows], got) <= TOL_BLOCKED
     assert np.array_equal(_np(dv.attention(0, n_tok, n_kb))[rows], got)
+    if n_tok >= 256 and c_z % 16 == 0:  # the tiled kernel: one part here, three in stripes of few rows
+        clean = Device(wl, affine=True)  # no NaN in the masked tokens' own rows
+        check_partitions(clean, 0, n_tok, clean.attention(0, n_tok, n_kb), n_kb=3)
     if n_tok > 20:  # a stripe, bf16 output
         sub = rows[(rows >= 3) & (rows < n_tok - 2)]
         out = _np(dv.attention(3, n_tok - 5, n_kb, out_dtype=DCP_BF16))[sub - 3]
@@ -135,6 +138,7 @@ def test_pad1024_blocked_vs_unblocked(torch_cuda):
         err = rel_err(b, a)
         log(f"  n_kb={nb} rel diff {err:.3e}")
         assert err <= TOL_BLOCKED
+    check_partitions(d, 0, 1024, d.attention(0, 1024, 4))
 
 
 def test_deterministic(torch_cuda):
@@ -174,9 +178,8 @@ def test_affine_constants_irrelevant(torch_cuda):
     (37, 5, 19, 3, "random:6"),
     (100, 60, 40, 5, "random:30"),
     (333, 0, 333, 2, "tail:13"),
-    # one workgroup of query rows over many keys: the launch splits the keys into
-    # many short parts whose bounds do not fall on 16-key tiles (32 parts of 64
-    # keys; 7 parts of 71-72 keys per block)
+    # few query rows over many keys: the launch splits the keys into many short
+    # parts of whole 16-key tiles, whatever the key blocks
     (2048, 100, 50, 1, "random:200"),
     (1500, 0, 64, 3, "tail:7"),
 ])
@@ -209,6 +212,7 @@ def test_one_block_entirely_masked(torch_cuda):
     got = _np(d.attention(0, 200, 4))
     assert rel_err(got, d.oracle_rows(np.arange(200))) <= TOL_BF16
     assert rel_err(got, _np(d.attention(0, 200, 1))) <= TOL_BLOCKED
+    check_partitions(d, 0, 200, d.attention(0, 200, 4))
 
 
 def test_n_q_zero_is_noop(torch_cuda):
@@ -260,6 +264,10 @@ def test_part_partition_edges(torch_cuda, n_tok, q_row0, n_q, n_kb):
     assert rel_err(got, d.oracle_rows(np.arange(q_row0, q_row0 + n_q))) <= TOL_BF16
     assert rel_err(_np(d.attention(q_row0, n_q, 1)), got) <= TOL_BLOCKED
     assert np.array_equal(_np(d.attention(q_row0, n_q, n_kb)), got)
+    if n_tok > 1000:
+        whole = d.attention(0, n_tok, 1)  # its rows are split into fewer parts
+        assert not torch_cuda.equal(whole[q_row0:q_row0 + n_q], d.attention(q_row0, n_q, n_kb))
+        assert rel_err(_np(whole[q_row0:q_row0 + n_q]), got) <= TOL_BLOCKED
 
 
 @pytest.mark.parametrize("n_tok,c_z,h,d,dtype,q_row0,n_q,n_kb", [

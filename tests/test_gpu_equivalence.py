@@ -2,9 +2,10 @@
 
 The paper keeps the sharded computation numerically equivalent to the
 single-GPU one (Introduction; Methods, "2D grid context parallelism"): here
-that means (1) the key-blocked result equals the unblocked one at the
-workloads whose launches split blocks differently (the 4800-token layer's 10
-blocks, a 12000-token stripe's 4 blocks each cut into segments), (2) the
+that means (1) a layer's rows do not depend on how the keys are partitioned:
+with one key block or several, in stripes of few rows (which the library
+splits into more parts) and as merged partial states of key ranges that meet
+inside its 16-key tiles (the 4800-token layer, a 12000-token stripe), (2) the
 fused LayerNorm holds for pair vectors whose channel mean is large against
 their spread, or whose scale is far from 1 (Methods, "RFDiffusion 3
 preliminaries and notation": the bias is a learned projection of Z, read as
@@ -20,7 +21,8 @@ import pytest
 
 import oracle
 import synth
-from gpu_helpers import AtomDevice, DCP_F32, Device, atom_workload, log, rel_err, sample_rows, workload
+from gpu_helpers import (AtomDevice, DCP_F32, Device, atom_workload, check_partitions, log, rel_err, sample_rows,
+                         workload)
 
 pytestmark = pytest.mark.gpu
 
@@ -48,6 +50,7 @@ def test_ico4800_blocked_vs_unblocked(torch_cuda):
     err = rel_err(b, a)
     log(f"  rel diff {err:.3e}")
     assert err <= TOL_BLOCKED
+    check_partitions(d, 0, wl.n_tok, d.attention(0, wl.n_tok, wl.n_key_blocks))
     rows = sample_rows(wl.n_tok, wl.stripes, wl.n_key_blocks, 24, d.mask_host, seed=3)
     assert rel_err(b[rows], d.oracle_rows(rows)) <= TOL_BF16
 
@@ -62,6 +65,7 @@ def test_grid12000_stripe_blocked_vs_unblocked(torch_cuda):
     err = rel_err(b, a)
     log(f"  rel diff {err:.3e}")
     assert err <= TOL_BLOCKED
+    check_partitions(d, q0, nq, d.attention(q0, nq, wl.n_key_blocks))
     rows = [q0, q0 + 1, q0 + nq // 2, q0 + nq - 1]
     assert rel_err(b[np.array(rows) - q0], d.oracle_rows(rows)) <= TOL_BF16
 
@@ -90,6 +94,7 @@ def test_layernorm_shift_scale_attention(torch_cuda, alpha, shift):
     assert err <= TOL_BF16
     # the same keys in one block: the blocked weights do not depend on the offset either
     assert rel_err(_np(d.attention(7, 290, 1)), got) <= TOL_BLOCKED
+    check_partitions(d, 7, 290, d.attention(7, 290, 3))
 
 
 @pytest.mark.parametrize("alpha,shift", LN_CASES)
@@ -191,3 +196,5 @@ def test_peaked_softmax(torch_cuda, dtype, q_k, b, tol):
     log(f"  rel err {err:.3e}")
     assert err <= tol
     assert rel_err(_np(d.attention(q0, nq, 1))[:nq], got) <= (TOL_BLOCKED if dtype == "bf16" else 1e-5)
+    if dtype == "bf16":
+        check_partitions(d, q0, nq, d.attention(q0, nq, nkb))

@@ -4,7 +4,7 @@ against the fp64 oracle, plus full-size properties (GPU)."""
 import numpy as np
 import pytest
 
-from gpu_helpers import DCP_BF16, DCP_F32, Device, log, rel_err, sample_rows, workload
+from gpu_helpers import DCP_BF16, DCP_F32, Device, check_partitions, log, rel_err, sample_rows, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -43,6 +43,7 @@ def test_asm24000_blocked_and_deterministic(big):
     err = rel_err(c.cpu().numpy(), a.cpu().numpy())
     log(f"  blocked vs unblocked rel diff {err:.3e}")
     assert err <= 1e-6
+    check_partitions(big, 0, wl.n_tok, a)
     # padding (masked) query rows still produce outputs; masked keys are never used
     assert torch.isfinite(a).all()
 
@@ -71,14 +72,12 @@ def test_asm24000_bias_project_full_rows(big, r0):
 
 @pytest.mark.parametrize("q_row0,n_q", [(0, 16384), (7000, 16400)])
 def test_asm24000_stripes_numbered_per_xcd(big, q_row0, n_q):
-    """Stripes of 256 and 257 row groups of 64: the smallest for which the
-    attention numbers its workgroups per XCD, and one that leaves XCD 0 one row
-    group more than the others. Against the whole-layer call (fp32 out, 1e-6:
-    the stripe's own segment count may differ) and the fp64 oracle (1e-2, bf16
-    inputs) on the first and last rows of the stripe and of its last row
-    groups."""
+    """Stripes of 1024 and 1025 row tiles of 16 (256 and 257 groups of 64). Against the
+    whole-layer call (fp32 out, 1e-6: the stripe's own part count may differ) and the
+    fp64 oracle (1e-2, bf16 inputs) on the first and last rows of the stripe and of
+    its last row groups."""
     wl = big.wl
-    log(f"case asm24000_bf16 stripe q_row0={q_row0} n_q={n_q} n_kb={wl.n_key_blocks} (per-XCD numbering)")
+    log(f"case asm24000_bf16 stripe q_row0={q_row0} n_q={n_q} n_kb={wl.n_key_blocks} ")
     full = big.attention(0, wl.n_tok, wl.n_key_blocks).cpu().numpy()
     got = big.attention(q_row0, n_q, wl.n_key_blocks).cpu().numpy()
     err = rel_err(got, full[q_row0:q_row0 + n_q])

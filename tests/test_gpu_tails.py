@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_helpers import Device, log, rel_err, workload
+from gpu_helpers import Device, check_partitions, log, rel_err, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,4 @@ def test_tails_attention(torch_cuda, kind):
     assert err <= TOL_BF16
     one = d.attention(0, n, 1).float().cpu().numpy().astype(np.float64)
     assert rel_err(got, one) <= TOL_BLOCKED
+    check_partitions(d, 0, n, d.attention(0, n, 3))
