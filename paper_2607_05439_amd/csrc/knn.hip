@@ -35,8 +35,8 @@
 // the lists are sorted once, at the end (bitonic network across lanes).
 // What bounds it: the selections' chains of compare, count and branch, and the
 // visits' loads, at 5 to 8 waves per SIMD. 24000 queries of 96000 candidates, k =
-// 128: 171 us, 238 when every full buffer was sorted and merged and four queries
-// shared a wave; 1000 of 1000: 22 us, 84.
+// 128: 157 us a call, 247 when every full buffer was sorted and merged and four
+// queries shared a wave; 1000 of 1000: 21 us, 74.
 // topk_merge_kernel: one wave per row, a rank merge of two sorted lists.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -615,16 +615,21 @@ hipError_t launch_knn_k(const KnnArgs& a, hipStream_t st) {
   }
   // One query per wave: the most waves for the selections' scalar chains to
   // overlap, and the shortest wave. Two share a wave's candidate loads where even
-  // that fills the chip more than twice (8192 waves at a time); beyond 128
-  // neighbours or across groups the selections weigh more and one stays faster:
-  //   queries / candidates, k        four per wave    two    one
-  //     5000 /  5000, 128                 116 us     88     51
-  //    24000 / 24000, 128                 261       113    124
-  //    24000 / 96000, 128                 202       171    174
-  //    20000 / 40000, 200                 367       242    206
-  //    15000 / 60000, 128, mode 2         661       488    407
-  if constexpr (KS == 2)
-    if (a.group_mode == 0 && a.n_q > 16384) return launch_knn_q<KS, 0, 2>(a, st);
+  // that fills the chip more than twice (8192 waves at a time); across groups
+  // the selections weigh more and one stays faster:
+  //   queries / candidates, k            one    two per wave
+  //     5000 /  5000, 128                 54     97 us
+  //    16000 / 16000, 128                 89     84
+  //    20000 / 20000, 128                 97     99
+  //    24000 / 24000, 128                122    119
+  //    24000 / 96000, 128                177    155
+  //    17000 / 17000, 200                155    144
+  //    24000 / 96000, 200                258    238
+  //    20000 / 60000, 128, mode 1        131    118
+  //    15000 / 60000, 128, mode 2        396    460
+  //    24000 / 96000, 128, mode 2        707    742
+  if (a.n_q > 16384 && a.group_mode != 2)
+    return a.group_mode == 1 ? launch_knn_q<KS, 1, 2>(a, st) : launch_knn_q<KS, 0, 2>(a, st);
   return a.group_mode == 1   ? launch_knn_q<KS, 1, 1>(a, st)
          : a.group_mode == 2 ? launch_knn_q<KS, 2, 1>(a, st)
                              : launch_knn_q<KS, 0, 1>(a, st);

@@ -187,8 +187,9 @@ def test_knn96k_sampled_rows_and_ring_form():
     same((run_i.cpu().numpy(), run_d.cpu().numpy()), (gi, gd), "ring form")
 
 
-@pytest.mark.parametrize("k,lattice", [(1, False), (64, False), (100, True), (128, False)])
-def test_two_queries_per_wave(k, lattice):
+@pytest.mark.parametrize("k,lattice,mode", [(1, False, 0), (64, False, 0), (100, True, 0), (128, False, 0),
+                                            (200, False, 0), (256, True, 0), (100, True, 1), (200, False, 1)])
+def test_two_queries_per_wave(k, lattice, mode):
     """More than 16384 queries run two per wave: whole lists against the same queries in stripes that
     run one per wave, and sampled rows against the oracle; an odd query count, a last step of a
     few candidates, and (lattice) distances that tie in every list."""
@@ -197,11 +198,14 @@ def test_two_queries_per_wave(k, lattice):
     x = (r.integers(0, 9, (n_c, 3)) if lattice else 40.0 * r.standard_normal((n_c, 3))).astype(np.float32)
     q = (r.integers(0, 9, (n_q, 3)) if lattice else 40.0 * r.standard_normal((n_q, 3))).astype(np.float32)
     q[:n_c] = x  # the first queries are the candidates
-    got = gpu_knn(q, x, k, c_index0=5, q_self0=0)
-    a, b = gpu_knn(q[:9000], x, k, c_index0=5, q_self0=0), gpu_knn(q[9000:], x, k, c_index0=5)
+    g = (np.arange(n_q) % n_c // 400).astype(np.int32)
+    gq, gc = (g, g[:n_c]) if mode else (None, None)
+    got = gpu_knn(q, x, k, 5, 0, gq, gc, mode)
+    a = gpu_knn(q[:9000], x, k, 5, 0, gq if gq is None else gq[:9000], gc, mode)
+    b = gpu_knn(q[9000:], x, k, 5, -1, gq if gq is None else gq[9000:], gc, mode)
     same(got, (np.concatenate([a[0], b[0]]), np.concatenate([a[1], b[1]])), "two per wave against one")
     rows = np.concatenate([np.arange(0, n_q, 97), [n_q - 2, n_q - 1]])
-    ri, rd = oracle.knn(q[rows], x, k)
+    ri, rd = oracle.knn(q[rows], x, k, group_q=None if gq is None else gq[rows], group_c=gc, group_mode=mode)
     same((got[0][rows], got[1][rows]), (np.where(ri < 0, ri, ri + 5), rd), "against the oracle")
 
 
