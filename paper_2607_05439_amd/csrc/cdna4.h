@@ -90,7 +90,9 @@ __device__ __forceinline__ void transpose_bias(float (&b)[16][4]) {
 // only make its own waits stricter, never looser, because vector-memory
 // loads complete in issue order.)
 constexpr uint32_t kRawBufferFlags = 0x00020000u;
-constexpr int kOutOfRange = 0x7FFFFF00;  // offset past every record: the load moves no data
+// An offset past every record: nothing is read from memory, and zeros arrive, in
+// the registers or, for a copy into LDS, there.
+constexpr int kOutOfRange = 0x7FFFFF00;
 
 // 16 bytes per lane from buffer r at byte offset voff into LDS at
 // lds_base + 16 * lane (lds_base: wave-uniform LDS byte address). Waits for

@@ -103,8 +103,8 @@ int fast_segments(int64_t n_tok, int64_t n_q, int32_t n_kb) {
 // Parts that the fused attention splits a key range into, at most max_parts. A
 // workgroup holds 16 query rows and two fit a CU, so a launch runs in rounds of
 // 512; what a part costs, in keys at the rate of a full round (0.31 us per key of
-// 512 workgroups, 6.75 TB/s), was fitted to sweeps of the part count on 200 to 24000
-// tokens: a full round its keys; a last, partial round r workgroups' share of
+// 512 workgroups, 6.75 TB/s, on the box of the sweeps), was fitted to sweeps of the
+// part count on 200 to 24000 tokens: a full round its keys; a last, partial round r workgroups' share of
 // the stream, but at least 0.45 of a round's time per key alone on a CU and 0.94
 // with two on some; each round 51 keys for its start and end; and each partial
 // state 0.0021 per row for writing and merging it. 1024 tokens: 54 us at 4 or 8
@@ -233,8 +233,8 @@ static int run_attention(const dcp_shape* shape, const dcp_weights* w, const voi
   if (path == kPathFast && k_len > 0) {
     if (small) {
       // no split weights: their room goes to the gate and to more parts, which a
-      // few query rows need to reach the whole chip (60 tokens 22.2 us in one part,
-      // 17.3 in four; 333 tokens 32.4 in the five of the layout, 29.6 in seven)
+      // few query rows need to reach the whole chip (60 tokens 22% less time in four
+      // parts than in one, 333 tokens 9% less in seven than in the layout's five)
       const size_t hd = (size_t)shape->n_heads * shape->head_dim, stats = (size_t)shape->n_heads * n_q * 4;
       L.off_g = L.off_ws;
       const size_t off = L.off_g + round_up((size_t)n_q * hd * 4, 256), acc = (size_t)n_q * hd * 4;

@@ -16,7 +16,7 @@ constexpr int kFastD = 24;     // head dim
 // without it
 constexpr float kFastShift = 192.0f;
 constexpr int kFastDp = 32;    // head dim padded to the MFMA k width
-constexpr int kTileQ = 16;     // query rows per wave
+constexpr int kTileQ = 16;     // query rows per workgroup of the fused attention, and per projection tile
 constexpr int kTileK = 16;     // keys per tile
 // 16 rows of z must be addressable with 31-bit byte offsets: 16 * N * 256 < 2^31
 constexpr int64_t kFastMaxTokens = 500000;

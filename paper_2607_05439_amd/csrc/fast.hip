@@ -195,11 +195,13 @@ __device__ __forceinline__ uint32_t tile_valid_bits(const_u32_ptr tv, int64_t t,
 // two workgroups fit a CU, and one wave's arithmetic hides behind the others'
 // streams. The bias comes out of LDS in the accumulator layout of QK^T.
 //
-// What bounds it: the z stream. A 3000-row stripe of 12000 tokens runs at 6.75
-// TB/s (1365 us), the rate of the same loads without arithmetic. The form
-// before it (a wave held all 16 heads of 16 rows, 490 registers and 160 KB of LDS,
-// one wave per SIMD) took 1510 us there, 67 us on 1024 tokens (54 now) and 50 us on
-// 333 (19.5 now), with the same bits over the same parts.
+// What bounds it: the z stream. On 24000 tokens it runs at 98% of the rate of the
+// same loads without arithmetic. Whole calls with the form before it (a wave held
+// all 16 heads of 16 rows, 490 registers and 160 KB of LDS, one wave per SIMD) and
+// with this one: a 3000-row stripe of 12000 tokens 1593 and 1479 us, 4800 tokens
+// 1016 and 972, 1024 tokens 90 and 72 (this kernel 53), 333 tokens 64 and 28 (14;
+// the small layers with the other steps made for them), with the same bits over
+// the same parts.
 //
 // k and v go straight from L2 to registers, one tile ahead, as ordinary loads
 // whose waits the compiler counts; for its counts to be exact the z copies into
@@ -303,8 +305,8 @@ __global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
   // which holds logical chunk (L%16) ^ row. The instruction offset 1024 i, which
   // moves the LDS and the global address alike, selects the slot's quarter, so
   // load i's vector offset is that of its rows minus 1024 i. An invalid key
-  // (masked, or outside the part) gets an out-of-range offset: its load moves no
-  // data, so every load is unconditional.
+  // (masked, or outside the part) gets an out-of-range offset: its load reads no
+  // memory, so every load is unconditional.
   const int64_t rows_here = min((int64_t)kTileQ, a.n_q - q0);
   const int row_bytes = (int)(a.n_tok * (kCz * 2));
   const __amdgpu_buffer_rsrc_t zres = __builtin_amdgcn_make_buffer_rsrc(
@@ -442,7 +444,7 @@ __global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
     kv_load(min(t + 1, t_end - 1));
     bits = bits_next;
   }
-  wait_vm<0>();  // the look-ahead copies (no data) before exit
+  wait_vm<0>();  // the look-ahead copies (out of range) before exit
 
   const int64_t row = q0 + n;
   if (row >= a.n_q) return;
@@ -515,7 +517,7 @@ __global__ void __launch_bounds__(64 * kWaves, 1) bias_ring_kernel(FastBiasArgs 
   float cst[4];
   bias_constants(a, n, g, cst);
 
-  // rows r0 .. r0+15 (those past n_rows fall outside the record range: no data)
+  // rows r0 .. r0+15 (those past n_rows fall outside the record range: zeros)
   const int64_t rows_here = min((int64_t)16, a.n_rows - r0);
   const int row_bytes = (int)(a.row_stride * 2);
   const __amdgpu_buffer_rsrc_t zres = __builtin_amdgcn_make_buffer_rsrc(
@@ -579,7 +581,7 @@ __global__ void __launch_bounds__(64 * kWaves, 1) bias_ring_kernel(FastBiasArgs 
         __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(a.out + (orw * a.n_cols + oc) * kH + 4 * (ochunk & 3)));
     }
   }
-  wait_vm<0>();  // the look-ahead loads past the chunk (no data) before exit
+  wait_vm<0>();  // the look-ahead loads past the chunk (out of range) before exit
 }
 
 // The same for row strides too long for 32-bit buffer offsets over 16 rows:

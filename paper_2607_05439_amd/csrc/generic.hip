@@ -282,7 +282,7 @@ struct RawZ<true> {
   }
 };
 
-constexpr int kGenWaves = 4;  // 8 were slower: 87 against 79 us (601 tokens, 128 channels), 88 against 82 (900, 32)
+constexpr int kGenWaves = 4;  // 8 were slower: 79 against 61 us (601 tokens, 128 channels, no mask), 66 against 54 (900, 32)
 
 // grid (rows / R, parts), 4 waves that share R query rows and take every fourth
 // tile of 16 keys of the part. Lane (n, g) holds key n of the tile.
@@ -298,11 +298,11 @@ constexpr int kGenWaves = 4;  // 8 were slower: 87 against 79 us (601 tokens, 12
 // The 16 lanes' and 4 waves' states meet in LDS, in a fixed order.
 // DP: the head size padded to a multiple of 4; c_z <= 16 CT.
 // What bounds it: the memory path's lookups. 601 tokens of 128 channels (183 MB of
-// z) take 68 us with the projection, the same rows at the rate of a large read
-// about 30; timing probes without the bias products, or with z or k and v always
+// z) take 62 us here and 77 a call with masked keys, the same rows at the rate of a
+// large read 27; timing probes without the bias products, or with z or k and v always
 // from the same addresses, gained 1 to 5 us each, but k and v in an order that
-// puts four lanes' pieces on one line gained 8 (75 before), and a z load's four
-// consecutive lanes still lie in four rows. With k and v row-major it took 106;
+// puts four lanes' pieces on one line gained 8, and a z load's four
+// consecutive lanes still lie in four rows. With k and v row-major a call took 106;
 // with a lane per key, its state in LDS and z read three times in 4-byte pieces,
 // 1810.
 template <int NH, int DP, int CT, bool BF16, int R>
@@ -542,9 +542,10 @@ __global__ void __launch_bounds__(64 * kGenWaves, 2) gen_attn_kernel(GenAttnArgs
 }
 
 // Two rows per workgroup share each k and v load: faster where z is small beside
-// them and there are rows for it (32 channels, 900 tokens: 60 against 82 us), but
+// them and there are rows for it (32 channels, no mask: 900 tokens 54 against 61 us,
+// though 700, where one row each takes little more than a round, 45 against 42), but
 // the second row's state does not fit the registers beside 64 or 128 channels
-// (601 tokens of 128: 109 against 79 us).
+// (601 tokens of 128: 75 against 61 us, of 64: 50 against 46).
 template <int NH, int DP, bool BF16>
 void gen_attn_launch(const GenAttnArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)a.n_q, (unsigned)a.n_parts), block(64 * kGenWaves);

@@ -372,8 +372,10 @@ size_t fast_proj_split_bytes(int32_t c_s) { return (size_t)4 * kOutTiles * (c_s 
 
 // One kernel up to 80 token tiles of 16 (both sides together), where the chain of
 // proj_kernel's k-steps and the split's launch weigh more than splitting the
-// weights again for every two tiles: a whole layer of 60 tokens 31.9 -> 22.4 us,
-// 333 38.4 -> 32.7, 500 40.9 -> 38.3; 700 (88 tiles) 48.9 -> 49.9, 1024 70.3 -> 72.6.
+// weights again for every two tiles. Whole layers over the same parts, two kernels
+// and one: 60 tokens 31.9 and 22.4 us, 333 38.4 and 32.7, 500 40.9 and 38.3; 700 (88
+// tiles) 48.9 and 49.9, 1024 70.3 and 72.6. (More parts in the freed room take 333
+// tokens to 28.1.)
 bool fast_proj_small(int64_t key_tiles, int64_t query_tiles) { return key_tiles + query_tiles <= kSmallMaxTiles; }
 
 hipError_t launch_fast_proj(const FastProjArgs& a, hipStream_t st) {

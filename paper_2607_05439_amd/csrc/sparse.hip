@@ -544,7 +544,7 @@ sparse_attn_kernel(SparseAttnArgs a) {
   b = __builtin_amdgcn_readfirstlane(wave_min(b));
   while (b != INT32_MAX) {
     // 1. compact the slots of block b; pad the list to a multiple of kPad with
-    //    out-of-range offsets (those loads move no data)
+    //    out-of-range offsets (those loads read no memory)
     int count = 0;
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
@@ -666,7 +666,7 @@ sparse_attn_kernel(SparseAttnArgs a) {
     wave_lds_sync();
 
     // 3. batches of K/V rows; the requests for the batch after the last one
-    //    read the extra padding of the list (no data), which keeps the number
+    //    read the extra padding of the list (out of range), which keeps the number
     //    of loads in flight the same on every path
     int prev[kUnroll];  // addresses of the V loads in flight
     offsets(0, prev);
@@ -733,13 +733,14 @@ hipError_t launch_attn(const SparseAttnArgs& a, hipStream_t st) {
 }
 
 // Up to 2048 queries there are at most two waves per SIMD, so nothing hides a
-// wave's chain of batches and registers are free: batches twice as long (500 to
-// 2000 queries, whole calls: 128 slots 16.3 -> 15.4 us, 200 slots 29.4 -> 27.5, fp32
-// 22.2 -> 20.0; four times as long gains no more). With more queries the other
-// waves hide it: 5000 queries 34.1 against 35.7, 24000 130 against 133. The bf16
-// kernel of up to 256 slots has as many registers, and waves, either way: the longer
-// batches serve it at any size (200 slots, 24000 of 48000 atoms 198.6 -> 191.8 us, 6000
-// 61.8 -> 59.6; fp32 92 against 93).
+// wave's chain of batches and registers are free: batches twice as long (whole
+// calls, 500 and 2000 queries: 128 slots 15.5 -> 14.5 us and 19.0 -> 18.4; fp32 18.5
+// -> 17.0 and 27.2 -> 26.8, 200 slots 25.0 -> 22.9 and 35.4 -> 35.0; four times as
+// long gains no more). With more queries the other waves hide it: 5000 queries 33.9
+// against 35.3, fp32 of 24000 232 against 245. The bf16 kernel of up to 256 slots has
+// as many registers, and waves, either way: the longer batches serve it at any size
+// (200 slots, 24000 of 48000 atoms 198.6 -> 191.8 us, 6000 61.8 -> 59.6; fp32 94.5
+// against 96.5).
 template <int KMAX>
 hipError_t launch_attn_width(const SparseAttnArgs& a, bool bf16, hipStream_t st) {
   const bool few = a.n_q <= 2048;

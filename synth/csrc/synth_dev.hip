@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256, 1) read_pattern_kernel(const uint16_t* __
   auto issue = [&](int64_t j) {
     const bool in = j < k1;
     const int jo = (int)j * 256;
-    const int none = 0x7FFFFF00;  // past every record: moves no data
+    const int none = 0x7FFFFF00;  // past every record: reads no memory
     pattern_key_loads(zres, in ? off[0] + jo : none, in ? off[1] + jo : none, in ? off[2] + jo : none,
                       in ? off[3] + jo : none, base + (uint32_t)(j % kPatRing) * 4096u);
   };

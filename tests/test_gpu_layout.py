@@ -88,8 +88,4 @@ def test_direct_to_lds_loads(probe):
     assert np.array_equal(o[:64], s[lane ^ 5])                    # lane L lands at base + 16 L
     assert np.array_equal(o[64:128], s[64 + (lane ^ 9)])          # destination above 64 KB
     assert np.array_equal(o[192:256], s[128 + (lane ^ 3)])        # near the top of 160 KB
-    oob = o[128:192]
-    zeros = np.all(oob == 0)
-    untouched = np.all(oob[:, 0].astype(np.uint32) == (0xDEAD0000 + 102400 // 16 + lane).astype(np.uint32))
-    print("out-of-range DMA:", "writes zeros" if zeros else "leaves LDS untouched" if untouched else "other")
-    assert zeros or untouched
+    assert np.all(o[128:192] == 0)  # out of range: zeros, which the small-layer projection relies on
