@@ -103,7 +103,7 @@ int fast_segments(int64_t n_tok, int64_t n_q, int32_t n_kb) {
 // Parts that the fused attention splits a key range into, at most max_parts. A
 // workgroup holds 16 query rows and two fit a CU, so a launch runs in rounds of
 // 512; what a part costs, in keys at the rate of a full round (0.31 us per key of
-// 512 workgroups, 6.75 TB/s, on the box of the sweeps), was fitted to sweeps of the
+// 512 workgroups, 6.75 TB/s, on the card of the sweeps), was fitted to sweeps of the
 // part count on 200 to 24000 tokens: a full round its keys; a last, partial round r workgroups' share of
 // the stream, but at least 0.45 of a round's time per key alone on a CU and 0.94
 // with two on some; each round 51 keys for its start and end; and each partial
