@@ -221,14 +221,6 @@ __device__ __forceinline__ void dma_key_counted(__amdgpu_buffer_rsrc_t r, int v0
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, p, 16, v3, 0, 3072, 2);
 }
 
-// Loads issued before this stay before it, and later ones after: the waits below
-// count on the first keys' copies, then k and v, then the copies of later keys. The
-// compiler need not see an order between a copy into LDS and a load into registers.
-__device__ __forceinline__ void pin_loads() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 // Wait until at most N loads are outstanding, then four 16-byte LDS reads.
 template <int N>
 __device__ __forceinline__ void read_key(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4 (&z)[4]) {
@@ -342,14 +334,18 @@ __global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
       kt[j] = __builtin_amdgcn_raw_buffer_load_b128(kres, 64 * n + 16 * g, so, 0);
       vt[j] = __builtin_amdgcn_raw_buffer_load_b128(vres, 16 * lane, so, 0);
     }
-    pin_loads();
+    asm volatile("" ::: "memory");
   };
 
-  pin_loads();
+  asm volatile("" ::: "memory");
   uint32_t slot = 0;
 #pragma unroll
   for (int p = 0; p < kRing; ++p) z_dma(t_begin, bits, p, p);
-  pin_loads();
+  // The first keys' copies before the first k and v, as in the loop (where the
+  // inline asm keeps the order): the waits count on it, and the compiler need not
+  // see an order between a copy into LDS and a load into registers.
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   kv_load(t_begin);
 
   bf16x8 whi[4], wlo[4];
@@ -440,7 +436,7 @@ __global__ void __launch_bounds__(256, 2) attn_kernel(FastAttnArgs a) {
         m[h0 + j] = mnew[j];
       }
     }
-    pin_loads();
+    asm volatile("" ::: "memory");
     kv_load(min(t + 1, t_end - 1));
     bits = bits_next;
   }
